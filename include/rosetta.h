@@ -156,7 +156,16 @@ rosetta_status rosetta_ksk_prepare(const uint64_t *ksk_std_dev, uint64_t *ksk_de
  * rosetta_pbs_workspace_bytes(params, batch) bytes, grown on demand and kept
  * per device until rosetta_shutdown(); calls sharing that workspace on one
  * device must therefore be serialised (one stream at a time), or use
- * rosetta_pbs_batch_ws with distinct workspaces. */
+ * rosetta_pbs_batch_ws with distinct workspaces.
+ *
+ * At N = 2048 and 4096 with l <= 3 and small enough digits, this call and
+ * every other one that rotates (all but rosetta_pbs_batch_noalloc) works with
+ * double-precision transforms, exactly: it expands the prepared key (to 3 or
+ * 4 times its size) into stream-ordered memory of its own, from a pool that
+ * keeps at most 4 GiB per device between calls and is given back by
+ * rosetta_shutdown().  Where that memory is not to be had, and while the
+ * stream is being captured, the modular transforms run instead, with the
+ * same output bits. */
 rosetta_status rosetta_pbs_batch(const uint64_t *lwe_in, const uint64_t *bsk_dev,
                                  const uint64_t *ksk_dev, const uint64_t *lut, uint64_t *lwe_out,
                                  size_t batch, const rosetta_params *params, void *stream);
@@ -175,7 +184,8 @@ rosetta_status rosetta_pbs_batch_ws(const uint64_t *lwe_in, const uint64_t *bsk_
 /* Allocation-free rosetta_pbs_batch, for callers that cannot allocate device
  * memory while they run: code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc.  Same arguments, layouts, validation and
- * output bits as rosetta_pbs_batch (the same two kernels run); the scratch
+ * output bits as rosetta_pbs_batch (its blind rotation always runs the
+ * modular transforms, which need no expanded key); the scratch
  * between them (the extracted ciphertexts, rosetta_pbs_workspace_bytes
  * bytes) is a static device array of ROSETTA_NOALLOC_SCRATCH_BYTES that
  * each GPU the library runs on holds until the process ends, and the

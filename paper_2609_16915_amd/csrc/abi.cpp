@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -13,6 +14,7 @@
 #include <string>
 #include <vector>
 
+#include "fft.hpp"
 #include "gl.hpp"
 #include "internal.hpp"
 #include "rosetta.h"
@@ -21,6 +23,8 @@ using namespace rosetta;
 
 static __device__ __align__(256) uint64_t twiddle_store[256 + 512 + 1024 + 2048 + 4096];
 static __device__ __align__(256) uint64_t psi_store[256 + 512 + 1024 + 2048 + 4096];
+// complex words of the double-precision transforms, N = 2048 then N = 4096
+static __device__ __align__(256) double fft_store[2 * (Fft<11>::TABLE + Fft<12>::TABLE)];
 
 namespace {
 
@@ -109,6 +113,7 @@ constexpr size_t TWIDDLE_STORE_WORDS = 256 + 512 + 1024 + 2048 + 4096;
 struct DeviceState {
   uint64_t *twiddle_base = nullptr;  // this device's copy of twiddle_store
   uint64_t *psi_base = nullptr;      // this device's copy of psi_store
+  double *fft_base = nullptr;        // this device's copy of fft_store
   std::map<uint32_t, uint64_t> ninv;  // N -> N^-1, present once uploaded
   void *workspace = nullptr;
   size_t workspace_bytes = 0;
@@ -122,6 +127,37 @@ uint32_t bitrev(uint32_t x, int bits) {
   for (int b = 0; b < bits; ++b)
     if (x & (1u << b)) r |= 1u << (bits - 1 - b);
   return r;
+}
+
+// Table of the double-precision transform (Fft::TABLE in fft.hpp): every
+// component rounded from the extended-precision cosine and sine.
+template <class F>
+std::vector<double> fft_table() {
+  std::vector<double> t(2 * (size_t)F::TABLE);
+  // word at: e(num / den) in turns
+  auto put = [&](int at, long long num, long long den) {
+    const long double x = 2.0L * 3.14159265358979323846264338327950288L *
+                          (long double)num / (long double)den;
+    t[2 * at] = (double)cosl(x);
+    t[2 * at + 1] = (double)sinl(x);
+  };
+  for (int s = F::S0; s < F::LOGC; s += 2)
+    for (int b = 0; b < (1 << s); ++b) {
+      // phi(s, b) = 2^-(s+2) + rev_s(b) / 2^s; a = e(phi / 2), b = e(phi / 4)
+      const long long phi = 1 + 4ll * bitrev((uint32_t)b, s), den = 4ll << s;
+      put(F::fwd_at(s) + b, phi, 2 * den);
+      put(F::fwd_at(s) + (1 << s) + b, phi, 4 * den);
+    }
+  for (int q = 2; q < F::Q_END; q += 2)
+    for (int k = 0; k < (1 << q); ++k) {
+      put(F::inv_at(q) + k, -k, 2ll << q);
+      put(F::inv_at(q) + (1 << q) + k, -k, 4ll << q);
+    }
+  for (int k = 0; k < F::T; ++k) {
+    if (F::ODD) put(F::LAST_AT + k, -k, F::C);
+    put(F::TWIST_AT + k, -k, 4ll * F::C);
+  }
+  return t;
 }
 
 rosetta_status get_tables(uint32_t N, Tables &out) {
@@ -146,6 +182,14 @@ rosetta_status get_tables(uint32_t N, Tables &out) {
       return hip_fail(e, "hipGetSymbolAddress(psi_store)");
     }
   }
+  if (!ds.fft_base) {
+    e = hipGetSymbolAddress((void **)&ds.fft_base, HIP_SYMBOL(fft_store));
+    if (e != hipSuccess) {
+      ds.fft_base = nullptr;
+      return hip_fail(e, "hipGetSymbolAddress(fft_store)");
+    }
+  }
+  double *fft = N == 2048 ? ds.fft_base : N == 4096 ? ds.fft_base + 2 * Fft<11>::TABLE : nullptr;
   uint64_t *dst = ds.twiddle_base + (N - 256);
   auto it = ds.ninv.find(N);
   if (it == ds.ninv.end()) {
@@ -201,11 +245,17 @@ rosetta_status get_tables(uint32_t N, Tables &out) {
     e = hipMemcpy(ds.psi_base + (N - 256), pw.data(), pw.size() * sizeof(u64),
                   hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(e, "hipMemcpy(psi powers)");
+    if (fft) {
+      const std::vector<double> t = N == 2048 ? fft_table<Fft<11>>() : fft_table<Fft<12>>();
+      e = hipMemcpy(fft, t.data(), t.size() * sizeof(double), hipMemcpyHostToDevice);
+      if (e != hipSuccess) return hip_fail(e, "hipMemcpy(transform table)");
+    }
     it = ds.ninv.emplace(N, gl_inv(N)).first;
   }
   out.zeta = dst;
   out.psi = ds.psi_base + (N - 256);
   out.ninv = it->second;
+  out.fft = fft;
   return ROSETTA_OK;
 }
 
@@ -328,11 +378,13 @@ static rosetta_status check_br_args(const uint64_t *lwe_in, const uint64_t *bsk_
   return ROSETTA_OK;
 }
 
-rosetta_status rosetta_pbs_batch_ws(const uint64_t *lwe_in, const uint64_t *bsk_dev,
-                                    const uint64_t *ksk_dev, const uint64_t *lut,
-                                    uint64_t *lwe_out, size_t batch,
-                                    const rosetta_params *params, void *workspace,
-                                    size_t workspace_bytes, void *stream) {
+}  // extern "C"
+
+rosetta_status rosetta::pbs_batch(const uint64_t *lwe_in, const uint64_t *bsk_dev,
+                                  const uint64_t *ksk_dev, const uint64_t *lut,
+                                  uint64_t *lwe_out, size_t batch, const rosetta_params *params,
+                                  void *workspace, size_t workspace_bytes, bool may_allocate,
+                                  void *stream) {
   rosetta_status st = check_params(params);
   if (st) return st;
   if (batch == 0) return ok();
@@ -355,11 +407,22 @@ rosetta_status rosetta_pbs_batch_ws(const uint64_t *lwe_in, const uint64_t *bsk_
   if ((st = get_tables(params->N, tb))) return st;
   uint64_t *big = (uint64_t *)workspace;
   hipError_t e = launch_blind_rotate(lwe_in, bsk_dev, lut, big, batch, *params, tb, BR_EXTRACT,
-                                     0, (hipStream_t)stream);
+                                     0, may_allocate, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "blind_rotate launch");
   e = launch_keyswitch(big, ksk_dev, lwe_out, batch, *params, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "keyswitch launch");
   return ok();
+}
+
+extern "C" {
+
+rosetta_status rosetta_pbs_batch_ws(const uint64_t *lwe_in, const uint64_t *bsk_dev,
+                                    const uint64_t *ksk_dev, const uint64_t *lut,
+                                    uint64_t *lwe_out, size_t batch,
+                                    const rosetta_params *params, void *workspace,
+                                    size_t workspace_bytes, void *stream) {
+  return rosetta::pbs_batch(lwe_in, bsk_dev, ksk_dev, lut, lwe_out, batch, params, workspace,
+                            workspace_bytes, true, stream);
 }
 
 rosetta_status rosetta_pbs_batch(const uint64_t *lwe_in, const uint64_t *bsk_dev,
@@ -389,7 +452,7 @@ rosetta_status rosetta_blind_rotate(const uint64_t *lwe_in, const uint64_t *bsk_
   Tables tb;
   if ((st = get_tables(params->N, tb))) return st;
   hipError_t e = launch_blind_rotate(lwe_in, bsk_dev, lut, glwe_out, batch, *params, tb, BR_GLWE,
-                                     0, (hipStream_t)stream);
+                                     0, true, (hipStream_t)stream);
   return e == hipSuccess ? ok() : hip_fail(e, "blind_rotate launch");
 }
 
@@ -406,7 +469,7 @@ rosetta_status rosetta_blind_rotate_extract(const uint64_t *lwe_in, const uint64
   Tables tb;
   if ((st = get_tables(params->N, tb))) return st;
   hipError_t e = launch_blind_rotate(lwe_in, bsk_dev, lut, big_out, batch, *params, tb,
-                                     BR_EXTRACT, 0, (hipStream_t)stream);
+                                     BR_EXTRACT, 0, true, (hipStream_t)stream);
   return e == hipSuccess ? ok() : hip_fail(e, "blind_rotate launch");
 }
 
@@ -514,7 +577,7 @@ rosetta_status rosetta_blind_rotate_glwe(const uint64_t *lwe_in, const uint64_t 
   Tables tb;
   if ((st = get_tables(params->N, tb))) return st;
   hipError_t e = launch_blind_rotate(lwe_in, bsk_dev, glwe_tp, out, tps, *params, tb,
-                                     extract ? BR_EXTRACT : BR_GLWE, (int)group,
+                                     extract ? BR_EXTRACT : BR_GLWE, (int)group, true,
                                      (hipStream_t)stream);
   return e == hipSuccess ? ok() : hip_fail(e, "blind_rotate_glwe launch");
 }
@@ -732,6 +795,7 @@ rosetta_status rosetta_shutdown(void) {
     kv.second.workspace = nullptr;
     kv.second.workspace_bytes = 0;
   }
+  release_fft_pools();
   (void)hipSetDevice(cur);
   return ok();
 }

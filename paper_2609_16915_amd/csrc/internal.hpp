@@ -32,9 +32,19 @@ struct Tables {
   // blind rotation that keeps its accumulator in the transform domain
   const uint64_t *psi;
   uint64_t ninv;
+  // complex words of the double-precision transform (Fft::TABLE, fft.hpp),
+  // N >= 2048; nullptr below
+  const double *fft;
 };
 
 enum BrMode { BR_GLWE = 0, BR_EXTRACT = 1 };
+
+// rosetta_pbs_batch_ws; may_allocate false keeps the whole call free of
+// device allocations.
+rosetta_status pbs_batch(const uint64_t *lwe_in, const uint64_t *bsk_dev, const uint64_t *ksk_dev,
+                         const uint64_t *lut, uint64_t *lwe_out, size_t batch,
+                         const rosetta_params *params, void *workspace, size_t workspace_bytes,
+                         bool may_allocate, void *stream);
 
 // Record the calling thread's error message (read by rosetta_last_error).
 void set_last_error(const char *msg);
@@ -43,10 +53,49 @@ hipError_t launch_bsk_prepare(const uint64_t *bsk_std, uint64_t *bsk_dev,
                               const rosetta_params &p, const Tables &tb, hipStream_t st);
 hipError_t launch_ksk_prepare(const uint64_t *ksk_std, uint64_t *ksk_dev,
                               const rosetta_params &p, hipStream_t st);
+// Blind rotation: with double-precision transforms where fft_pieces allows
+// them and the key can be expanded into memory of the call's own (not while
+// the stream is being captured, and only if the caller allows allocations),
+// else with the modular ones.
 hipError_t launch_blind_rotate(const uint64_t *lwe_in, const uint64_t *bsk_dev,
                                const uint64_t *lut, uint64_t *out, size_t batch,
                                const rosetta_params &p, const Tables &tb, BrMode mode,
-                               int tp_glwe, hipStream_t st);
+                               int tp_glwe, bool may_allocate, hipStream_t st);
+hipError_t launch_blind_rotate_ntt(const uint64_t *lwe_in, const uint64_t *bsk_dev,
+                                   const uint64_t *lut, uint64_t *out, size_t batch,
+                                   const rosetta_params &p, const Tables &tb, BrMode mode,
+                                   int tp_glwe, hipStream_t st);
+// Give the expanded keys' memory back to the devices.
+void release_fft_pools();
+
+// Pieces per key coefficient of the double-precision blind rotation: 3 of 22
+// bits, 4 of 16, or 0 where only the modular transforms are exact.
+//
+// Error bound, u = 2^-53, M = log2(N/2) stages, R = 2l rows.  A butterfly's
+// sum is off by at most u(2|a| + 3|b|), its difference by u(3|a| + 4|b|)
+// (inputs a, b; roundings and the twiddle's own u), in the 2-norm 4.4 u of
+// the outputs, so the transforms of a digit polynomial d and of a piece k
+// are off by 4.4 M u relative each; the R complex products summed by fused
+// multiply-adds add 2.9 R u of sum |D||K| per point; and a coefficient of
+// the inverse is off by at most (4 (M - 2) + 2 + 7) u of the mean over
+// points of sum |D||K| (every path's roundings, the final twist included),
+// which is at most sum ||d|| ||k|| (Cauchy-Schwarz and Parseval).  Together
+// 146 u at N = 2048 and 158 u at N = 4096 for R = 6: 160 u.  With |d| <=
+// 2^(beta-1) and |k| <= 2^(b-1), ||d|| ||k|| <= N 2^(beta + b - 2), hence
+//   error <= 2 l N 2^(beta + b - 2) 160 2^-53, wanted <= 1/4.
+// No input can exceed it: the bound holds for every digit and key word.
+inline int fft_pieces(const rosetta_params &p) {
+  if ((p.N != 2048 && p.N != 4096) || p.pbs_level > 3) return 0;
+  auto holds = [&](unsigned bits) {
+    const unsigned e = p.pbs_base_log + bits - 2;
+    return e < 40 && ((uint64_t)2 * p.pbs_level * p.N * 160 << e) >> e ==
+                         (uint64_t)2 * p.pbs_level * p.N * 160 &&
+           (uint64_t)2 * p.pbs_level * p.N * 160 << e <= (uint64_t)1 << 51;
+  };
+  if (p.pbs_level * p.pbs_base_log <= 30 && holds(22)) return 3;
+  if (holds(16)) return 4;
+  return 0;
+}
 hipError_t launch_rows_prepare(const uint64_t *rows_std, uint64_t *rows_dev, size_t rows,
                                uint32_t N, const Tables &tb, hipStream_t st);
 hipError_t launch_trace(const uint64_t *in, const uint64_t *autk_dev, uint64_t *out,

@@ -157,15 +157,6 @@ struct KeyRows {
   }
 };
 
-// Coefficient j of X^r * v (negacyclic), 0 <= r < 2N.
-template <int N>
-__device__ __forceinline__ u64 rotated_coef(const u64 *v, int j, int r) {
-  const int rr = r & (N - 1);
-  const bool neg = (j < rr) != (r >= N);
-  const u64 x = v[(j - rr) & (N - 1)];
-  return neg ? gl_neg(x) : x;
-}
-
 // Key rows per chunk at the four-wave budget, and the scheduling fence
 // between chunks (see br_levels).
 #ifndef BR_KEY_CHUNK
@@ -932,10 +923,10 @@ static hipError_t launch_br_levels(const uint64_t *lwe_in, const uint64_t *bsk_d
   return hipSuccess;
 }
 
-hipError_t launch_blind_rotate(const uint64_t *lwe_in, const uint64_t *bsk_dev,
-                               const uint64_t *lut, uint64_t *out, size_t batch,
-                               const rosetta_params &p, const Tables &tb, BrMode mode,
-                               int tp_glwe, hipStream_t st) {
+hipError_t launch_blind_rotate_ntt(const uint64_t *lwe_in, const uint64_t *bsk_dev,
+                                   const uint64_t *lut, uint64_t *out, size_t batch,
+                                   const rosetta_params &p, const Tables &tb, BrMode mode,
+                                   int tp_glwe, hipStream_t st) {
   hipError_t e = hipSuccess;
   const int tpg = tp_glwe;
 #define ROSETTA_BR_L(LV)                                                                       \

@@ -79,8 +79,8 @@ extern "C" rosetta_status rosetta_pbs_batch_noalloc(const uint64_t *lwe_in,
     }
     ptr = it->second;
   }
-  // the two kernels of rosetta_pbs_batch_ws, with this device's scratch as
+  // the kernels of rosetta_pbs_batch_ws that allocate nothing, with this device's scratch as
   // the workspace (the twiddle tables live in static device memory too)
-  return rosetta_pbs_batch_ws(lwe_in, bsk_dev, ksk_dev, lut, lwe_out, batch, params, ptr,
-                              ROSETTA_NOALLOC_SCRATCH_BYTES, stream);
+  return rosetta::pbs_batch(lwe_in, bsk_dev, ksk_dev, lut, lwe_out, batch, params, ptr,
+                            ROSETTA_NOALLOC_SCRATCH_BYTES, false, stream);
 }

@@ -764,6 +764,15 @@ __device__ __forceinline__ void load_twiddles(u64 *tw_lds, const u64 *__restrict
   for (int i = tid; i < S::TW_WORDS; i += S::T) tw_lds[i] = zeta[i];
 }
 
+// Coefficient j of X^r * v (negacyclic), 0 <= r < 2N.
+template <int N>
+__device__ __forceinline__ u64 rotated_coef(const u64 *v, int j, int r) {
+  const int rr = r & (N - 1);
+  const bool neg = (j < rr) != (r >= N);
+  const u64 x = v[(j - rr) & (N - 1)];
+  return neg ? gl_neg(x) : x;
+}
+
 // Global-address-space view of a device pointer.
 __device__ __forceinline__ gconst_u64 *as_global(const u64 *p) { return (gconst_u64 *)p; }
 

@@ -1,0 +1,128 @@
+"""Blind rotation with double-precision transforms (N >= 2048) against the
+modular one and the oracle, bit for bit, at the edges of the rule that
+chooses between them: the largest digits of every case it accepts and the
+first it does not, with key words, ciphertexts and tables of extreme values,
+on one ciphertext and on more than the device holds at once.  The modular
+kernels run where nothing may be allocated (rosetta_pbs_batch_noalloc, a
+stream under capture)."""
+import numpy as np
+import pytest
+
+from paper_2609_16915_amd import rosetta as R
+from test_fft_exact_cpu import pieces
+
+from gpu_helpers import require_gpu, say
+
+pytestmark = pytest.mark.gpu
+P = R.P
+EDGES = np.array([0, 1, 2, P - 1, P - 2, (P - 1) // 2, (P + 1) // 2, 1 << 21, (1 << 21) - 1, 1 << 43,
+                  P - (1 << 43), (1 << 63) - 1, 1 << 63, 0x200000800002000, P - 0x200000800002000,
+                  0xFFFFFFFF, 1 << 32], dtype=np.uint64)
+
+
+def _cases():
+    out = []
+    for N in (2048, 4096):
+        for l in (1, 2, 3):
+            for want in (3, 4):
+                out.append((N, l, max(b for b in range(1, 31) if pieces(N, l, b) == want)))
+            out.append((N, l, min(b for b in range(1, 31) if pieces(N, l, b) == 0)))
+        out.append((N, 3, 1))
+        out.append((N, 4, 8))
+    return out
+
+
+def _params(N, l, beta, n):
+    return dict(n=n, k=1, N=N, pbs_level=l, pbs_base_log=beta, ks_level=3, ks_base_log=4, msg_bits=4)
+
+
+def _words(rng, *shape):
+    x = rng.integers(0, P, shape, dtype=np.uint64)
+    return np.where(rng.random(shape) < 0.3, EDGES[rng.integers(0, len(EDGES), shape)], x)
+
+
+@pytest.mark.parametrize("N,l,beta", _cases())
+def test_equals_the_modular_transforms(O, N, l, beta):
+    torch = require_gpu()
+    prm = _params(N, l, beta, 5)
+    rng = np.random.default_rng(N + 100 * l + beta)
+    # a key whose words are extremes in long runs as well as at random
+    bsk_std = _words(rng, R.bsk_words(prm))
+    bsk_std[: 2 * N] = (P - 1) // 2
+    bsk_std[2 * N: 4 * N] = (P + 1) // 2
+    ksk_std = rng.integers(0, P, R.ksk_words(prm), dtype=np.uint64)
+    bsk = R.bsk_prepare(R.to_device(bsk_std), prm)
+    ksk = R.ksk_prepare(R.to_device(ksk_std), prm)
+    lut = _words(rng, N)
+    d_lut = R.to_device(lut)
+    op = O.Params.make(**{k: v for k, v in prm.items() if k != "k"})
+    for batch in (1, 1100):
+        say(f"[fft] N={N} l={l} beta={beta} batch {batch}")
+        cts = _words(rng, batch, prm["n"] + 1)
+        d_in = R.to_device(cts)
+        out = R.to_host(R.pbs_batch(d_in, bsk, ksk, d_lut, prm))
+        ref = R.empty((batch, prm["n"] + 1))
+        R.pbs_batch_noalloc(d_in, bsk, ksk, d_lut, prm, ref)
+        assert np.array_equal(out, R.to_host(ref))
+        pick = sorted({0, batch // 2, batch - 1})
+        assert np.array_equal(out[pick], O.pbs(op, cts[pick], bsk_std, ksk_std, lut, O.NTT))
+        # GLWE output, ciphertext test polynomials
+        tp = _words(rng, 2 * batch, 2 * N)
+        got = R.to_host(R.blind_rotate_glwe(d_in, bsk, R.to_device(tp), prm, group=2))
+        if batch == 1:
+            want = O.blind_rotate_glwe_batch(op, np.repeat(cts, 2, axis=0), bsk_std, tp, O.NTT)
+            assert np.array_equal(got, want.reshape(got.shape))
+    torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("N,l,beta", [(2048, 3, 8), (4096, 2, 13)])
+def test_capture_runs_the_modular_kernels(N, l, beta):
+    """A captured call (nothing may be allocated) replays to the eager call's
+    bits, with eager calls and new inputs between the replays."""
+    torch = require_gpu()
+    prm = _params(N, l, beta, 7)
+    rng = np.random.default_rng(3)
+    bsk = R.bsk_prepare(R.to_device(rng.integers(0, P, R.bsk_words(prm), dtype=np.uint64)), prm)
+    ksk = R.ksk_prepare(R.to_device(rng.integers(0, P, R.ksk_words(prm), dtype=np.uint64)), prm)
+    lut = R.to_device(_words(rng, N))
+    batch = 3
+    ws = R.empty(R.pbs_workspace_bytes(prm, batch) // 8)
+    d_in = R.to_device(_words(rng, batch, prm["n"] + 1))
+    out = R.empty((batch, prm["n"] + 1))
+    say(f"[fft] capture N={N}")
+    eager = R.to_host(R.pbs_batch(d_in, bsk, ksk, lut, prm))
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        R.pbs_batch_ws(d_in, bsk, ksk, lut, prm, ws, out=out)
+    for seed in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(R.to_host(out), eager)
+        d_in.copy_(R.to_device(_words(np.random.default_rng(seed), batch, prm["n"] + 1)))
+        eager = R.to_host(R.pbs_batch(d_in, bsk, ksk, lut, prm))
+
+
+def test_streams_hold_their_own_expanded_keys():
+    """Calls with different keys overlapping on several streams, repeated so
+    that the memory of the expanded keys is reused, each give their own
+    bits."""
+    torch = require_gpu()
+    prm = _params(2048, 3, 8, 40)
+    rng = np.random.default_rng(9)
+    lut = R.to_device(_words(rng, 2048))
+    jobs = []
+    for batch in (5, 300, 70):
+        bsk = R.bsk_prepare(R.to_device(rng.integers(0, P, R.bsk_words(prm), dtype=np.uint64)), prm)
+        d_in = R.to_device(_words(rng, batch, prm["n"] + 1))
+        want = R.to_host(R.blind_rotate_extract(d_in, bsk, lut, prm))
+        jobs.append((torch.cuda.Stream(), bsk, d_in, R.empty(want.shape), want))
+    torch.cuda.synchronize()
+    for round_ in range(3):
+        for st, bsk, d_in, out, _ in jobs:
+            R.blind_rotate_extract(d_in, bsk, lut, prm, out=out, stream=st)
+    for st, _, _, out, want in jobs:
+        st.synchronize()
+        assert np.array_equal(R.to_host(out), want)
+    R.shutdown()  # gives the pool back; the next call makes it anew
+    _, bsk, d_in, _, want = jobs[0]
+    assert np.array_equal(R.to_host(R.blind_rotate_extract(d_in, bsk, lut, prm)), want)
