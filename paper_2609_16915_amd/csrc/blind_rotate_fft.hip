@@ -329,12 +329,12 @@ k_blind_rotate_fft(const u64 *__restrict__ lwe_in, const cd *__restrict__ key,
       }
     };
     // a5: group g (sum g / ROWS, row g % ROWS) into its sum
-    cd Y[2][1][4];
+    cd Y[2][4];
     const ExpandedRows G(key + (size_t)i * step_words);
     auto group = [&](auto gc) {
       constexpr int g = decltype(gc)::value;
       constexpr int r = g % ROWS, sum = g / ROWS;
-      cd(&y)[4] = Y[sum & 1][0];
+      cd(&y)[4] = Y[sum & 1];
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const cd w = q[g % PD][k];
@@ -397,13 +397,13 @@ k_blind_rotate_fft(const u64 *__restrict__ lwe_in, const cd *__restrict__ key,
     u32 top[8];
     static_for<0, SUMS>([&](auto sc) {
       constexpr int S = decltype(sc)::value, c = S / P, p = S % P;
-      cd(&y)[1][4] = Y[S & 1];
+      cd(&y)[4] = Y[S & 1];
       // The wave's own blocks first: in odd LOGC the same words again, read
       // by the others before the barrier of the last exchange (in O2); in
       // even LOGC two sets of words in turn, the others' last reads of one
       // lie before the barrier of the other.
       constexpr int O1 = F::ODD ? 0 : (S & 1) * C, O2 = C;
-      fft_inverse<F, 1, 0, O1, O2>(y, ln, [&](auto h) {
+      fft_inverse<F, 0, O1, O2>(y, ln, [&](auto h) {
         if constexpr (S + 1 < SUMS)
           groups(std::integral_constant<int, (S + 1) * ROWS>{},
                  std::integral_constant<int, ROWS>{}, h,
@@ -411,8 +411,8 @@ k_blind_rotate_fft(const u64 *__restrict__ lwe_in, const cd *__restrict__ key,
       });
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        add_piece<P, p>(acc[c][k], top[k], y[0][k].re);
-        add_piece<P, p>(acc[c][k + 4], top[k + 4], y[0][k].im);
+        add_piece<P, p>(acc[c][k], top[k], y[k].re);
+        add_piece<P, p>(acc[c][k + 4], top[k + 4], y[k].im);
       }
       if constexpr (p == P - 1) {
 #pragma unroll

@@ -221,23 +221,25 @@ __device__ __forceinline__ int fft_word(const Lane &ln, int k) {
   const int o = UP ? ln.base : X == 1 ? ln.plus_h : ln.plus_w;
   return k > 0 ? fft_xor(o, 16 * (X == 1 ? 4 * k : k)) : o;
 }
-template <class F, int X, bool DOWN, int NB, int OFF, class Lane>
-__device__ __forceinline__ void fft_wave_exchange(cd (&x)[NB][4], const Lane &ln) {
-  wave_sync();
+// The four slots' words on one side of an exchange, and one transform's data
+// to and from there (words off .. of the buffer).
+template <int X, bool UP>
+struct FftWords {
+  int w[4];
+  template <class Lane>
+  __device__ __forceinline__ explicit FftWords(const Lane &ln) {
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int w = fft_word<X, DOWN>(ln, k);
-#pragma unroll
-    for (int b = 0; b < NB; ++b) fft_put(w, 16 * (OFF + b * F::C + (DOWN ? 16 * k : 0)), x[b][k]);
+    for (int k = 0; k < 4; ++k) w[k] = fft_word<X, UP>(ln, k);
   }
-  wave_sync();
+  __device__ __forceinline__ void put(const cd (&x)[4], int off) const {
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int r = fft_word<X, !DOWN>(ln, k);
-#pragma unroll
-    for (int b = 0; b < NB; ++b) x[b][k] = fft_get(r, 16 * (OFF + b * F::C + (DOWN ? 0 : 16 * k)));
+    for (int k = 0; k < 4; ++k) fft_put(w[k], 16 * (off + (UP ? 16 * k : 0)), x[k]);
   }
-}
+  __device__ __forceinline__ void get(cd (&x)[4], int off) const {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x[k] = fft_get(w[k], 16 * (off + (UP ? 16 * k : 0)));
+  }
+};
 
 // Layouts across waves: 0 the natural one (j = t + T k); 1 (odd LOGC) slot
 // bits (9,8); 2 slot bits (7,6), the wave's own block.
@@ -251,23 +253,15 @@ template <class F, int LY>
 constexpr int fft_step() {
   return LY == 0 ? F::T : LY == 1 ? 256 : 64;
 }
-// Every wave has to be done reading what the writes overwrite (a barrier
-// before, or words nobody else reads); hook(H) fills the wait for the
-// barrier, the caller what follows the reads.
-template <class F, int LA, int LB, int NB, int OFF, int H, class Lane, class Hook>
-__device__ __forceinline__ void fft_cross_exchange(cd (&x)[NB][4], const Lane &ln,
-                                                   const Hook &hook) {
-  const int w = fft_at<F, LA>(ln), r = fft_at<F, LB>(ln);
+template <class F, int LY, class Lane>
+__device__ __forceinline__ void fft_put_cross(const cd (&x)[4], int off, const Lane &ln) {
 #pragma unroll
-  for (int b = 0; b < NB; ++b)
+  for (int k = 0; k < 4; ++k) fft_put(fft_at<F, LY>(ln), 16 * (off + k * fft_step<F, LY>()), x[k]);
+}
+template <class F, int LY, class Lane>
+__device__ __forceinline__ void fft_get_cross(cd (&x)[4], int off, const Lane &ln) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) fft_put(w, 16 * (OFF + b * F::C + k * fft_step<F, LA>()), x[b][k]);
-  hook(std::integral_constant<int, H>{});
-  __syncthreads();
-#pragma unroll
-  for (int b = 0; b < NB; ++b)
-#pragma unroll
-    for (int k = 0; k < 4; ++k) x[b][k] = fft_get(r, 16 * (OFF + b * F::C + k * fft_step<F, LB>()));
+  for (int k = 0; k < 4; ++k) x[k] = fft_get(fft_at<F, LY>(ln), 16 * (off + k * fft_step<F, LY>()));
 }
 
 // cos, sin of 1/8 and 1/16 of a turn
@@ -278,102 +272,144 @@ constexpr double FFT_C8 = 0.70710678118654752440, FFT_C16 = 0.923879532511286756
 // The table starts at byte TAB of the LDS, the buffer where ln says; the
 // transforms use words [0, NB C) of it and start with a barrier.
 // hook(0 .. HOOKS - 1) runs where the wave waits for the LDS or the others.
+// Each transform is written as soon as its pass is done and the next one's
+// pass follows, so that the LDS works while the VALU does.
 template <class F, int NB, int TAB, class Lane, class Hook>
 __device__ __forceinline__ void fft_forward(cd (&x)[NB][4], const Lane &ln, const Hook &hook) {
-  constexpr int H0 = F::ODD ? 2 : 0;
-  auto pass = [&](int at, int stages, int block16) {
-    const cd a = fft_get(block16, TAB + 16 * at), b = fft_get(block16, TAB + 16 * (at + (1 << stages)));
-#pragma unroll
-    for (int i = 0; i < NB; ++i) fft_fwd4(x[i], a, b);
+  constexpr int H0 = F::ODD ? 2 : 0, C = F::C;
+  struct Tw {
+    cd a, b;
   };
+  auto twiddles = [&](int at, int stages, int block16) {
+    return Tw{fft_get(block16, TAB + 16 * at), fft_get(block16, TAB + 16 * (at + (1 << stages)))};
+  };
+  auto first = [&](cd (&z)[4]) {
+    if constexpr (F::ODD) {
+      fft_bfly(z[0], z[2], FFT_C8, FFT_C8);
+      fft_bfly(z[1], z[3], FFT_C8, FFT_C8);
+    } else {
+      fft_fwd4(z, cd{FFT_C8, FFT_C8}, cd{FFT_C16, FFT_S16});
+    }
+  };
+  first(x[0]);
+  __syncthreads();
+  static_for<0, NB>([&](auto bc) {
+    constexpr int b = decltype(bc)::value;
+    if constexpr (b > 0) first(x[b]);
+    fft_put_cross<F, 0>(x[b], b * C, ln);
+  });
+  hook(std::integral_constant<int, 0>{});
+  __syncthreads();
   if constexpr (F::ODD) {
+    const Tw w = twiddles(F::fwd_at(1), 1, fft_and(fft_shr(ln.t16, 8), ~15));
+#pragma unroll
+    for (int b = 0; b < NB; ++b) fft_get_cross<F, 1>(x[b], b * C, ln);
+    hook(std::integral_constant<int, 1>{});
+    fft_fwd4(x[0], w.a, w.b);
+    __syncthreads();
+    static_for<0, NB>([&](auto bc) {
+      constexpr int b = decltype(bc)::value;
+      if constexpr (b > 0) fft_fwd4(x[b], w.a, w.b);
+      fft_put_cross<F, 1>(x[b], b * C, ln);
+    });
+    hook(std::integral_constant<int, 2>{});
+    __syncthreads();
+  }
+  {
+    const Tw w = twiddles(F::fwd_at(F::LOGC - 8), F::LOGC - 8, fft_and(fft_shr(ln.t16, 6), ~15));
+    const Tw v = twiddles(F::fwd_at(F::LOGC - 6), F::LOGC - 6, fft_and(fft_shr(ln.t16, 4), ~15));
+#pragma unroll
+    for (int b = 0; b < NB; ++b) fft_get_cross<F, 2>(x[b], b * C, ln);
+    hook(std::integral_constant<int, H0 + 1>{});
+    const FftWords<1, true> up(ln);
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
-      fft_bfly(x[b][0], x[b][2], FFT_C8, FFT_C8);
-      fft_bfly(x[b][1], x[b][3], FFT_C8, FFT_C8);
+      fft_fwd4(x[b], w.a, w.b);
+      fft_lane_swap(x[b]);
+      fft_fwd4(x[b], v.a, v.b);
+      up.put(x[b], b * C);
     }
-    __syncthreads();
-    fft_cross_exchange<F, 0, 1, NB, 0, 0>(x, ln, hook);
-    hook(std::integral_constant<int, 1>{});
-    pass(F::fwd_at(1), 1, fft_and(fft_shr(ln.t16, 8), ~15));
-    __syncthreads();
-    fft_cross_exchange<F, 1, 2, NB, 0, H0>(x, ln, hook);
-  } else {
-#pragma unroll
-    for (int b = 0; b < NB; ++b) fft_fwd4(x[b], cd{FFT_C8, FFT_C8}, cd{FFT_C16, FFT_S16});
-    __syncthreads();
-    fft_cross_exchange<F, 0, 2, NB, 0, H0>(x, ln, hook);
   }
-  hook(std::integral_constant<int, H0 + 1>{});
-  pass(F::fwd_at(F::LOGC - 8), F::LOGC - 8, fft_and(fft_shr(ln.t16, 6), ~15));
+  {
+    const Tw w = twiddles(F::fwd_at(F::LOGC - 4), F::LOGC - 4, fft_and(fft_shr(ln.t16, 2), ~15));
+    const FftWords<1, false> lo(ln);
+    const FftWords<2, true> up(ln);
+    wave_sync();
 #pragma unroll
-  for (int b = 0; b < NB; ++b) fft_lane_swap(x[b]);
-  pass(F::fwd_at(F::LOGC - 6), F::LOGC - 6, fft_and(fft_shr(ln.t16, 4), ~15));
-  fft_wave_exchange<F, 1, true, NB, 0>(x, ln);
-  hook(std::integral_constant<int, H0 + 2>{});
-  pass(F::fwd_at(F::LOGC - 4), F::LOGC - 4, fft_and(fft_shr(ln.t16, 2), ~15));
-  fft_wave_exchange<F, 2, true, NB, 0>(x, ln);
+    for (int b = 0; b < NB; ++b) lo.get(x[b], b * C);
+    hook(std::integral_constant<int, H0 + 2>{});
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      fft_fwd4(x[b], w.a, w.b);
+      up.put(x[b], b * C);
+    }
+  }
+  const Tw w = twiddles(F::fwd_at(F::LOGC - 2), F::LOGC - 2, ln.t16);
+  const FftWords<2, false> lo(ln);
+  wave_sync();
+#pragma unroll
+  for (int b = 0; b < NB; ++b) lo.get(x[b], b * C);
   hook(std::integral_constant<int, H0 + 3>{});
-  pass(F::fwd_at(F::LOGC - 2), F::LOGC - 2, ln.t16);
+#pragma unroll
+  for (int b = 0; b < NB; ++b) fft_fwd4(x[b], w.a, w.b);
 }
 
-// NB inverse transforms (times C) side by side: slot bits (1,0) in, natural
-// layout out.  They work in the wave's own blocks of words [O1, O1 + NB C) of
-// the buffer, which nobody else may read any more, write those once more, and
-// read all of them after a barrier; for odd LOGC a second exchange goes
-// through words [O2, O2 + NB C), which have to be free once that barrier is
-// passed.
-template <class F, int NB, int TAB, int O1, int O2, class Lane, class Hook>
-__device__ __forceinline__ void fft_inverse(cd (&x)[NB][4], const Lane &ln, const Hook &hook) {
+// The inverse transform (times C): slot bits (1,0) in, natural layout out.
+// It works in the wave's own block of words [O1, O1 + C) of the buffer,
+// which nobody else may read any more, writes it once more, and reads all of
+// those words after a barrier; for odd LOGC a second exchange goes through
+// words [O2, O2 + C), which have to be free once that barrier is passed.
+template <class F, int TAB, int O1, int O2, class Lane, class Hook>
+__device__ __forceinline__ void fft_inverse(cd (&x)[4], const Lane &ln, const Hook &hook) {
   constexpr int H0 = F::ODD ? 6 : 4;
   auto pass = [&](int at, int bits, int pos16) {
     const cd a = fft_get(pos16, TAB + 16 * at), v = fft_get(pos16, TAB + 16 * (at + (1 << bits)));
-#pragma unroll
-    for (int i = 0; i < NB; ++i) fft_inv4(x[i], a, v);
+    fft_inv4(x, a, v);
   };
-#pragma unroll
-  for (int b = 0; b < NB; ++b) fft_inv4_first(x[b]);
-  fft_wave_exchange<F, 2, false, NB, O1>(x, ln);
+  fft_inv4_first(x);
+  wave_sync();
+  FftWords<2, false>(ln).put(x, O1);
+  wave_sync();
+  FftWords<2, true>(ln).get(x, O1);
   hook(std::integral_constant<int, 0>{});
   pass(F::inv_at(2), 2, fft_and(ln.t16, 48));
-  fft_wave_exchange<F, 1, false, NB, O1>(x, ln);
+  wave_sync();
+  FftWords<1, false>(ln).put(x, O1);
+  wave_sync();
+  FftWords<1, true>(ln).get(x, O1);
   hook(std::integral_constant<int, 1>{});
   pass(F::inv_at(4), 4, fft_and(ln.t16, 240));
-#pragma unroll
-  for (int b = 0; b < NB; ++b) fft_lane_swap(x[b]);
+  fft_lane_swap(x);
   pass(F::inv_at(6), 6, fft_and(ln.t16, 1008));
   wave_sync();
+  fft_put_cross<F, 2>(x, O1, ln);
+  hook(std::integral_constant<int, 2>{});
+  __syncthreads();
   if constexpr (F::ODD) {
-    fft_cross_exchange<F, 2, 1, NB, O1, 2>(x, ln, hook);
+    fft_get_cross<F, 1>(x, O1, ln);
     hook(std::integral_constant<int, 3>{});
     pass(F::inv_at(8), 8, fft_and(ln.t16, 4080));
-    fft_cross_exchange<F, 1, 0, NB, O2, 4>(x, ln, hook);
+    fft_put_cross<F, 1>(x, O2, ln);
+    hook(std::integral_constant<int, 4>{});
+    __syncthreads();
+    fft_get_cross<F, 0>(x, O2, ln);
   } else {
-    fft_cross_exchange<F, 2, 0, NB, O1, 2>(x, ln, hook);
+    fft_get_cross<F, 0>(x, O1, ln);
   }
   hook(std::integral_constant<int, H0 - 1>{});
   if constexpr (F::ODD) {
     const cd w = fft_get(ln.t16, TAB + 16 * F::LAST_AT);
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      fft_bfly(x[b][0], x[b][2], w.re, w.im);
-      fft_bfly(x[b][1], x[b][3], w.im, -w.re);
-    }
+    fft_bfly(x[0], x[2], w.re, w.im);
+    fft_bfly(x[1], x[3], w.im, -w.re);
   } else {
     pass(F::inv_at(8), 8, ln.t16);
   }
   // e(-(t + T k) / 4C) = e(-t / 4C) e(-k / 16)
   const cd w0 = fft_get(ln.t16, TAB + 16 * F::TWIST_AT);
-  const cd w1 = fft_mul(w0, cd{FFT_C16, -FFT_S16});
-  const cd w2 = fft_mul(w0, cd{FFT_C8, -FFT_C8});
-  const cd w3 = fft_mul(w0, cd{FFT_S16, -FFT_C16});
-#pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    x[b][0] = fft_mul(x[b][0], w0);
-    x[b][1] = fft_mul(x[b][1], w1);
-    x[b][2] = fft_mul(x[b][2], w2);
-    x[b][3] = fft_mul(x[b][3], w3);
-  }
+  x[0] = fft_mul(x[0], w0);
+  x[1] = fft_mul(x[1], fft_mul(w0, cd{FFT_C16, -FFT_S16}));
+  x[2] = fft_mul(x[2], fft_mul(w0, cd{FFT_C8, -FFT_C8}));
+  x[3] = fft_mul(x[3], fft_mul(w0, cd{FFT_S16, -FFT_C16}));
 }
 
 }  // namespace rosetta
