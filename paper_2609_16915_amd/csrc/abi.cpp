@@ -409,7 +409,7 @@ rosetta_status rosetta::pbs_batch(const uint64_t *lwe_in, const uint64_t *bsk_de
   hipError_t e = launch_blind_rotate(lwe_in, bsk_dev, lut, big, batch, *params, tb, BR_EXTRACT,
                                      0, may_allocate, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "blind_rotate launch");
-  e = launch_keyswitch(big, ksk_dev, lwe_out, batch, *params, (hipStream_t)stream);
+  e = launch_keyswitch(big, ksk_dev, lwe_out, batch, *params, may_allocate, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "keyswitch launch");
   return ok();
 }
@@ -484,7 +484,8 @@ rosetta_status rosetta_keyswitch(const uint64_t *big_in, const uint64_t *ksk_dev
   if (any_overlap(lwe_out, out_bytes, big_in, batch * ((size_t)params->N + 1) * 8) ||
       any_overlap(lwe_out, out_bytes, ksk_dev, rosetta_ksk_device_words(params) * 8))
     return fail(ROSETTA_ERR_ALIAS, "output overlaps an input");
-  hipError_t e = launch_keyswitch(big_in, ksk_dev, lwe_out, batch, *params, (hipStream_t)stream);
+  hipError_t e =
+      launch_keyswitch(big_in, ksk_dev, lwe_out, batch, *params, true, (hipStream_t)stream);
   return e == hipSuccess ? ok() : hip_fail(e, "keyswitch launch");
 }
 
@@ -795,7 +796,7 @@ rosetta_status rosetta_shutdown(void) {
     kv.second.workspace = nullptr;
     kv.second.workspace_bytes = 0;
   }
-  release_fft_pools();
+  scratch_release();
   (void)hipSetDevice(cur);
   return ok();
 }

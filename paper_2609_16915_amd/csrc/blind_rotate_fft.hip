@@ -10,8 +10,6 @@
 // kernels.hip for every input.
 #include <hip/hip_runtime.h>
 
-#include <map>
-#include <mutex>
 #include <type_traits>
 
 #include "fft.hpp"
@@ -195,7 +193,6 @@ template <int L>
 constexpr int key_ahead() {
   return L == 3 ? 3 : 4;
 }
-constexpr int KEY_AHEAD_MAX = 4;
 // Complex words of the exchange buffer: the L digit polynomials of a
 // component, two sums, or the two components of the rotation.
 template <class F, int L>
@@ -266,7 +263,7 @@ k_blind_rotate_fft(const u64 *__restrict__ lwe_in, const cd *__restrict__ key,
   constexpr int ROWS = 2 * L, SUMS = 2 * P;
   // a multiple of the ring per step keeps its places compile-time constants
   constexpr int PD = key_ahead<L>();
-  static_assert((SUMS * ROWS) % PD == 0 && PD <= KEY_AHEAD_MAX, "whole turns of the ring");
+  static_assert((SUMS * ROWS) % PD == 0, "whole turns of the ring");
   constexpr bool PARK = L == 3;
   // ring of key groups (a sum's row), loaded PD ahead of their use
   cd q[PD][4];
@@ -459,36 +456,6 @@ hipError_t allow_lds(K kernel, size_t bytes) {
                              (int)bytes);
 }
 
-// The expanded key of a launch comes from one stream-ordered pool per
-// device, so that calls on several streams or threads each have their own.
-// The pool keeps what was freed, up to POOL_KEEP, between calls;
-// release_fft_pools gives it back.
-constexpr uint64_t POOL_KEEP = (uint64_t)4 << 30;
-std::mutex g_pool_mu;
-std::map<int, hipMemPool_t> g_pools;
-
-hipError_t device_pool(hipMemPool_t *out) {
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  std::lock_guard<std::mutex> lock(g_pool_mu);
-  auto it = g_pools.find(dev);
-  if (it == g_pools.end()) {
-    hipMemPoolProps props{};
-    props.allocType = hipMemAllocationTypePinned;
-    props.handleTypes = hipMemHandleTypeNone;
-    props.location.type = hipMemLocationTypeDevice;
-    props.location.id = dev;
-    hipMemPool_t pool;
-    if ((e = hipMemPoolCreate(&pool, &props)) != hipSuccess) return e;
-    uint64_t keep = POOL_KEEP;
-    (void)hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep);
-    it = g_pools.emplace(dev, pool).first;
-  }
-  *out = it->second;
-  return hipSuccess;
-}
-
 template <class S, class F, int L, int P, typename RT>
 hipError_t launch_fft(const uint64_t *lwe_in, const uint64_t *bsk_dev, const uint64_t *lut,
                       uint64_t *out, size_t batch, const rosetta_params &p, const Tables &tb,
@@ -497,9 +464,9 @@ hipError_t launch_fft(const uint64_t *lwe_in, const uint64_t *bsk_dev, const uin
   const size_t lds = br_fft_lds_bytes<F, L>((int)p.n);
   hipError_t e;
   if ((e = allow_lds(k_expand_key<S, F, P>, xlds)) != hipSuccess) return e;
-  if ((e = allow_lds(k_blind_rotate_fft<F, L, P, RT>, lds)) != hipSuccess) return e;
   hipLaunchKernelGGL((k_expand_key<S, F, P>), dim3(p.n), dim3(S::T), xlds, st, bsk_dev, key, L,
                      tb.zeta, (const cd *)tb.fft);
+  if ((e = allow_lds(k_blind_rotate_fft<F, L, P, RT>, lds)) != hipSuccess) return e;
   hipLaunchKernelGGL((k_blind_rotate_fft<F, L, P, RT>), dim3(batch), dim3(F::T), lds, st, lwe_in,
                      key, lut, out, (int)p.n, (int)p.pbs_base_log, mode, tp_glwe,
                      (const cd *)tb.fft);
@@ -532,37 +499,25 @@ hipError_t launch_fft_levels(const uint64_t *lwe_in, const uint64_t *bsk_dev, co
 
 }  // namespace
 
-void release_fft_pools() {
-  std::lock_guard<std::mutex> lock(g_pool_mu);
-  for (auto &kv : g_pools) (void)hipMemPoolTrimTo(kv.second, 0);
-}
-
 hipError_t launch_blind_rotate(const uint64_t *lwe_in, const uint64_t *bsk_dev,
                                const uint64_t *lut, uint64_t *out, size_t batch,
                                const rosetta_params &p, const Tables &tb, BrMode mode,
                                int tp_glwe, bool may_allocate, hipStream_t st) {
   const int pieces = may_allocate ? fft_pieces(p) : 0;
   if (pieces) {
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    hipMemPool_t pool;
-    void *key = nullptr;
-    // the key stream is read KEY_AHEAD_MAX groups past its end
-    const size_t bytes = ((size_t)p.n * 2 * pieces * 2 * p.pbs_level + KEY_AHEAD_MAX) *
-                         (p.N / 2) * sizeof(cd);
-    if (hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
-        device_pool(&pool) == hipSuccess &&
-        hipMallocFromPoolAsync(&key, bytes, pool, st) == hipSuccess) {
+    // (one step more: the key stream is loaded ahead of its use)
+    const size_t bytes =
+        ((size_t)p.n + 1) * 2 * pieces * 2 * p.pbs_level * (p.N / 2) * sizeof(cd);
+    if (void *key = scratch_take(bytes, st)) {
       const hipError_t e = p.N == 2048
                                ? launch_fft_levels<11>(lwe_in, bsk_dev, lut, out, batch, p, tb,
                                                        (int)mode, tp_glwe, (cd *)key, st)
                                : launch_fft_levels<12>(lwe_in, bsk_dev, lut, out, batch, p, tb,
                                                        (int)mode, tp_glwe, (cd *)key, st);
-      const hipError_t f = hipFreeAsync(key, st);
+      const hipError_t f = scratch_give(key, st);
       return e != hipSuccess ? e : f;
     }
-    // being captured, or no memory for the expanded key: the modular
-    // transforms need none
-    if (cap == hipStreamCaptureStatusNone) (void)hipGetLastError();
+    // the modular transforms need no expanded key
   }
   return launch_blind_rotate_ntt(lwe_in, bsk_dev, lut, out, batch, p, tb, mode, tp_glwe, st);
 }

@@ -46,6 +46,9 @@ rosetta_status pbs_batch(const uint64_t *lwe_in, const uint64_t *bsk_dev, const 
                          const rosetta_params *params, void *workspace, size_t workspace_bytes,
                          bool may_allocate, void *stream);
 
+// Compute units of the current device (0 if unknown).
+int device_cus();
+
 // Record the calling thread's error message (read by rosetta_last_error).
 void set_last_error(const char *msg);
 
@@ -65,8 +68,13 @@ hipError_t launch_blind_rotate_ntt(const uint64_t *lwe_in, const uint64_t *bsk_d
                                    const uint64_t *lut, uint64_t *out, size_t batch,
                                    const rosetta_params &p, const Tables &tb, BrMode mode,
                                    int tp_glwe, hipStream_t st);
-// Give the expanded keys' memory back to the devices.
-void release_fft_pools();
+// Device memory for one call on stream st (scratch.cpp): nullptr where it is
+// not to be had, the stream being captured included.  scratch_give returns it
+// once the work enqueued so far is done; scratch_release gives what the pools
+// keep back to the devices.
+void *scratch_take(size_t bytes, hipStream_t st);
+hipError_t scratch_give(void *p, hipStream_t st);
+void scratch_release();
 
 // Pieces per key coefficient of the double-precision blind rotation: 3 of 22
 // bits, 4 of 16, or 0 where only the modular transforms are exact.
@@ -134,7 +142,8 @@ hipError_t launch_field_op(int op, const uint64_t *a, const uint64_t *b, const u
 hipError_t launch_modmul_chain(uint64_t seed, uint32_t threads, uint32_t iters, uint64_t *out,
                                hipStream_t st);
 hipError_t launch_keyswitch(const uint64_t *big, const uint64_t *ksk_dev, uint64_t *out,
-                            size_t batch, const rosetta_params &p, hipStream_t st);
+                            size_t batch, const rosetta_params &p, bool may_allocate,
+                            hipStream_t st);
 
 // The key switch is one integer matrix product over the batch (digits x
 // key), run on the int8 matrix cores when the signed digits fit a byte

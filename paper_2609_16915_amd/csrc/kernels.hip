@@ -879,7 +879,7 @@ hipError_t launch_bsk_prepare(const uint64_t *bsk_std, uint64_t *bsk_dev,
 
 // Compute units of the current device (cached per device; 0 if unknown,
 // which keeps every batch on the throughput instance).
-static int device_cus() {
+int device_cus() {
   static std::atomic<int> cus[64];
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
