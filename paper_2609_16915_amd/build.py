@@ -15,7 +15,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "librosetta.so")
-SOURCES = ["kernels.hip", "blind_rotate_fft.hip", "keyswitch.hip", "lwe_ops.hip", "abi.cpp", "scratch.cpp", "noalloc.hip",
+SOURCES = ["kernels.hip", "exact_fft.hip", "keyswitch.hip", "lwe_ops.hip", "abi.cpp", "scratch.cpp", "noalloc.hip",
            "host_helpers.cpp", "seglut.cpp", "lookup.cpp"]
 ARCH = os.environ.get("ROSETTA_OFFLOAD_ARCH", "gfx950")
 

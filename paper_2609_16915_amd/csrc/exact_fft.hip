@@ -1,6 +1,7 @@
-// Blind rotation with double-precision transforms (see fft.hpp), exact.
+// Blind rotation and trace with double-precision transforms (see fft.hpp),
+// exact.
 //
-// The products of a CMux step, digits x key row, are exact integers that
+// The products of a step, digits x key row, are exact integers that
 // only have to be known modulo p, so the transform need not be modular: each
 // centred key coefficient is cut into P balanced pieces of PB bits, every
 // digit polynomial is transformed once in double precision, multiplied with
@@ -31,14 +32,16 @@ constexpr int piece_bits() {
 // Key expansion: prepared (modular) rows -> transforms of their pieces
 // ---------------------------------------------------------------------------
 
-// One workgroup per GGSW.  Row (u, t, c) of the prepared key goes back to
-// coefficients (its N^-1 scaling makes the plain inverse exact), each is
-// centred and cut into P balanced pieces, and the pieces are transformed.
-// Expanded layout, in complex words: [i][c][p][r = u L + t][slot k][thread],
-// scaled by 1/C (a power of two, exact), as the products read it.
+// Workgroups (step, y): a step is a GGSW or a round of the trace, of which
+// workgroup y takes every gridDim.y-th row.  Row (r, c) of the
+// prepared key, r < R, goes back to coefficients (its N^-1 scaling makes the
+// plain inverse exact), each is centred and cut into P balanced pieces, and
+// the pieces are transformed.  Expanded layout, in complex words:
+// [step][c][p][r][slot k][thread], scaled by +-1/C (a power of two, exact), as
+// the products read it.
 template <class S, class F, int P>
 __global__ void __launch_bounds__(S::T)
-k_expand_key(const u64 *__restrict__ bsk, cd *__restrict__ out, int L,
+k_expand_key(const u64 *__restrict__ prepared, cd *__restrict__ out, int R, double scale,
              const u64 *__restrict__ zeta, const cd *__restrict__ fft_tab) {
   static_assert(S::T == F::T && S::E == 8, "one thread layout for both transforms");
   constexpr int N = S::N, T = S::T, C = F::C, PB = piece_bits<P>();
@@ -51,10 +54,10 @@ k_expand_key(const u64 *__restrict__ bsk, cd *__restrict__ out, int L,
   load_twiddles<S>(tw, zeta, tid);
   for (int i = tid; i < F::TABLE; i += T) tab[i] = fft_tab[i];
   __syncthreads();
-  const int rows = 4 * L;
+  const int rows = 2 * R;
 #pragma unroll 1
-  for (int row = 0; row < rows; ++row) {
-    const u64 *src = bsk + ((size_t)blockIdx.x * rows + row) * N;
+  for (int row = blockIdx.y; row < rows; row += gridDim.y) {
+    const u64 *src = prepared + ((size_t)blockIdx.x * rows + row) * N;
     u64 x[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) x[k] = gl_canon(src[k * T + tid]);
@@ -78,12 +81,12 @@ k_expand_key(const u64 *__restrict__ bsk, cd *__restrict__ out, int L,
           d[h] = p == P - 1 ? w : (i64)((u64)w << (64 - PB)) >> (64 - PB);
           w = (w - d[h]) >> PB;
         }
-        z[0][k] = cd{(double)d[0] * (1.0 / C), (double)d[1] * (1.0 / C)};
+        z[0][k] = cd{(double)d[0] * scale, (double)d[1] * scale};
       }
       // the transform opens with a barrier, so the last reads of the buffer
       // are over
       fft_forward<F, 1, 0>(z, ln, NoHook{});
-      cd *o = out + (((size_t)(blockIdx.x * 2 + c) * P + p) * (2 * L) + r) * C + tid;
+      cd *o = out + (((size_t)(blockIdx.x * 2 + c) * P + p) * R + r) * C + tid;
 #pragma unroll
       for (int k = 0; k < 4; ++k) o[k * T] = z[0][k];
     }
@@ -191,7 +194,13 @@ __device__ __forceinline__ u64 finish_pieces(u64 acc, u32 top) {
 // 100.5 ms.
 template <int L>
 constexpr int key_ahead() {
-  return L == 3 ? 3 : 4;
+  return L == 3 ? 3 : 2;
+}
+// Sums taken back side by side: two where fewer rows leave the registers
+// (l = 2, 1536 GPT-2 ciphertexts: 35.8 ms, one sum and 4 groups 36.9 ms).
+template <int L>
+constexpr int sums_at_once() {
+  return L == 3 ? 1 : 2;
 }
 // Complex words of the exchange buffer: the L digit polynomials of a
 // component, two sums, or the two components of the rotation.
@@ -262,7 +271,7 @@ k_blind_rotate_fft(const u64 *__restrict__ lwe_in, const cd *__restrict__ key,
   constexpr size_t step_words = (size_t)2 * P * 2 * L * C;
   constexpr int ROWS = 2 * L, SUMS = 2 * P;
   // a multiple of the ring per step keeps its places compile-time constants
-  constexpr int PD = key_ahead<L>();
+  constexpr int PD = key_ahead<L>(), NB = sums_at_once<L>();
   static_assert((SUMS * ROWS) % PD == 0, "whole turns of the ring");
   constexpr bool PARK = L == 3;
   // ring of key groups (a sum's row), loaded PD ahead of their use
@@ -326,12 +335,12 @@ k_blind_rotate_fft(const u64 *__restrict__ lwe_in, const cd *__restrict__ key,
       }
     };
     // a5: group g (sum g / ROWS, row g % ROWS) into its sum
-    cd Y[2][4];
+    cd Y[2][NB][4];
     const ExpandedRows G(key + (size_t)i * step_words);
     auto group = [&](auto gc) {
       constexpr int g = decltype(gc)::value;
       constexpr int r = g % ROWS, sum = g / ROWS;
-      cd(&y)[4] = Y[sum & 1];
+      cd(&y)[4] = Y[(sum / NB) & 1][sum % NB];
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const cd w = q[g % PD][k];
@@ -368,7 +377,7 @@ k_blind_rotate_fft(const u64 *__restrict__ lwe_in, const cd *__restrict__ key,
       groups(std::integral_constant<int, 0>{}, std::integral_constant<int, L>{}, h,
              std::integral_constant<int, F::FWD_HOOKS>{});
     });
-    static_for<L, ROWS>(group);
+    static_for<L, NB * ROWS>(group);
     // Three levels leave no registers for both components of the accumulator
     // next to three key groups in flight: the one whose sums are not being
     // taken back waits in the wave's own block of the buffer's third part,
@@ -389,38 +398,43 @@ k_blind_rotate_fft(const u64 *__restrict__ lwe_in, const cd *__restrict__ key,
       }
     };
     if constexpr (PARK) put(1);
-    // a6: sum S goes back to coefficients while the next one's groups are
+    // a6: NB sums go back to coefficients while the next ones' groups are
     // added up
     u32 top[8];
-    static_for<0, SUMS>([&](auto sc) {
-      constexpr int S = decltype(sc)::value, c = S / P, p = S % P;
-      cd(&y)[4] = Y[S & 1];
-      // The wave's own blocks first: in odd LOGC the same words again, read
-      // by the others before the barrier of the last exchange (in O2); in
-      // even LOGC two sets of words in turn, the others' last reads of one
-      // lie before the barrier of the other.
-      constexpr int O1 = F::ODD ? 0 : (S & 1) * C, O2 = C;
-      fft_inverse<F, 0, O1, O2>(y, ln, [&](auto h) {
-        if constexpr (S + 1 < SUMS)
-          groups(std::integral_constant<int, (S + 1) * ROWS>{},
-                 std::integral_constant<int, ROWS>{}, h,
+    static_for<0, SUMS / NB>([&](auto bc) {
+      constexpr int B = decltype(bc)::value;
+      cd(&y)[NB][4] = Y[B & 1];
+      // The wave's own blocks first.  One sum: in odd LOGC the same words
+      // again, read by the others before the barrier of the last exchange (in
+      // O2); in even LOGC two sets of words in turn, the others' last reads of
+      // one lie before the barrier of the other.  Two sums: one set of words,
+      // which a barrier opens again.
+      constexpr bool ONE = NB > 1;
+      constexpr int O1 = F::ODD || ONE ? 0 : (B & 1) * C, O2 = ONE ? 0 : C;
+      fft_inverse<F, NB, 0, O1, O2, ONE && (B > 0)>(y, ln, [&](auto h) {
+        if constexpr (B + 1 < SUMS / NB)
+          groups(std::integral_constant<int, (B + 1) * NB * ROWS>{},
+                 std::integral_constant<int, NB * ROWS>{}, h,
                  std::integral_constant<int, F::INV_HOOKS>{});
       });
+      static_for<0, NB>([&](auto jc) {
+        constexpr int j = decltype(jc)::value, S = B * NB + j, c = S / P, p = S % P;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        add_piece<P, p>(acc[c][k], top[k], y[k].re);
-        add_piece<P, p>(acc[c][k + 4], top[k + 4], y[k].im);
-      }
-      if constexpr (p == P - 1) {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) acc[c][k] = finish_pieces(acc[c][k], top[k]);
-        if constexpr (PARK && c == 0) {
-          get(1);
-          put(0);
-        } else if constexpr (PARK) {
-          get(0);
+        for (int k = 0; k < 4; ++k) {
+          add_piece<P, p>(acc[c][k], top[k], y[j][k].re);
+          add_piece<P, p>(acc[c][k + 4], top[k + 4], y[j][k].im);
         }
-      }
+        if constexpr (p == P - 1) {
+#pragma unroll
+          for (int k = 0; k < 8; ++k) acc[c][k] = finish_pieces(acc[c][k], top[k]);
+          if constexpr (PARK && c == 0) {
+            get(1);
+            put(0);
+          } else if constexpr (PARK) {
+            get(0);
+          }
+        }
+      });
     });
   }
 
@@ -444,6 +458,165 @@ k_blind_rotate_fft(const u64 *__restrict__ lwe_in, const cd *__restrict__ key,
 }
 
 // ---------------------------------------------------------------------------
+// Trace
+// ---------------------------------------------------------------------------
+
+// Digit polynomials transformed side by side: two at a time where there are
+// four, so that two workgroups' buffers fit a CU's LDS.
+template <int L>
+constexpr int trace_batch() {
+  return L == 4 ? 2 : L;
+}
+template <class F, int L>
+constexpr size_t trace_fft_lds_bytes() {
+  return F::TABLE_BYTES + (size_t)(trace_batch<L>() > 2 ? trace_batch<L>() : 2) * F::C * sizeof(cd);
+}
+
+// The rounds of k_trace (kernels.hip) with the machinery of
+// k_blind_rotate_fft: the L digit polynomials of tau_d(A), the 2P sums over
+// their rows (the expanded key carries the minus sign of the key switch),
+// taken back one after the other while the next is added up.
+// Bound as there: VALU issue, and the waits of eight inverse transforms a
+// round with less to fill them (4 rows a sum).  14336 traces at N = 2048, 4 x
+// 12 bits (4 pieces): 6.0 ms (6.1 with one sum at a time), 7.5 ms with modular
+// transforms; 3 x 10 bits (3 pieces) 4.3 against 6.2, N = 4096 15.5 against
+// 24.1 ms; one trace 167 against 258 us.
+template <class F, int L, int P>
+__global__ void __launch_bounds__(F::T) __attribute__((amdgpu_waves_per_eu(2, 2)))
+k_trace_fft(const u64 *__restrict__ in, const cd *__restrict__ key, u64 *__restrict__ out,
+            int beta, u64 ninv, const cd *__restrict__ fft_tab) {
+  constexpr int N = F::N, C = F::C, T = F::T;
+  cd *tab = (cd *)fft_lds;
+  u64 *w = (u64 *)(tab + F::TABLE_BYTES / 16);
+  const int tid = threadIdx.x;
+  const FftLane<F::TABLE_BYTES> ln(tid);
+  const size_t ct = blockIdx.x;
+  for (int i = tid; i < F::TABLE; i += T) tab[i] = fft_tab[i];
+
+  u64 acc[2][8];
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int k = 0; k < 8; ++k) acc[c][k] = gl_mul(in[(ct * 2 + c) * N + tid + T * k], ninv);
+
+  const int s = 64 - L * beta;
+  const i64 half = (i64)1 << (beta - 1);
+  const int dsh = 64 - beta;
+  constexpr int SUMS = 2 * P, GROUPS = SUMS * L, FB = trace_batch<L>();
+  constexpr int NB = 2, PD = 2;  // sums side by side, key groups in flight
+  static_assert(GROUPS % PD == 0 && L % FB == 0, "whole turns of the ring, whole batches");
+  constexpr size_t round_words = (size_t)GROUPS * C;
+  cd q[PD][4];
+  {
+    const ExpandedRows G(key + (F::LOGN - 1) * round_words);
+#pragma unroll
+    for (int g = 0; g < PD; ++g)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) q[g][k] = G.load(tid * 16, (g * C + k * T) * 16);
+  }
+#pragma unroll 1
+  for (int kr = F::LOGN; kr >= 1; --kr) {
+    const u32 dinv = odd_inverse_mod((1u << kr) + 1, 2 * N);
+    cd D[L / FB][FB][4];
+    {
+      __syncthreads();
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int k = 0; k < 8; ++k) w[c * N + tid + T * k] = acc[c][k];
+      __syncthreads();
+      i64 R[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) R[k] = gl_round_top(automorphism_coef<N>(w, tid + T * k, dinv), s);
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        acc[1][k] = gl_add(acc[1][k], automorphism_coef<N>(w + N, tid + T * k, dinv));
+#pragma unroll
+      for (int t = L - 1; t >= 0; --t)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          int32_t e[2];
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            i64 &r = R[k + 4 * h];
+            if (t == 0) {
+              e[h] = (int32_t)r;
+            } else {
+              e[h] = (int32_t)((i64)((u64)r << dsh) >> dsh);
+              r = (r + half) >> beta;
+            }
+          }
+          D[t / FB][t % FB][k] = cd{(double)e[0], (double)e[1]};
+        }
+    }
+    cd Y[2][NB][4];
+    const ExpandedRows G(key + (kr - 1) * round_words);
+    // the groups loaded past this round's belong to the next one's
+    const ExpandedRows Gn(key + (kr > 1 ? kr - 2 : 0) * round_words);
+    auto group = [&](auto gc) {
+      constexpr int g = decltype(gc)::value, r = g % L, nx = g + PD;
+      cd(&y)[4] = Y[(g / L / NB) & 1][g / L % NB];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const cd z = q[g % PD][k];
+        const cd x = D[r / FB][r % FB][k];
+        if (r == 0) {
+          y[k].re = __builtin_fma(-x.im, z.im, x.re * z.re);
+          y[k].im = __builtin_fma(x.im, z.re, x.re * z.im);
+        } else {
+          y[k].re = __builtin_fma(-x.im, z.im, __builtin_fma(x.re, z.re, y[k].re));
+          y[k].im = __builtin_fma(x.im, z.re, __builtin_fma(x.re, z.im, y[k].im));
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        q[g % PD][k] = (nx < GROUPS ? G : Gn).load(tid * 16, ((nx % GROUPS) * C + k * T) * 16);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    fft_forward<F, FB, 0>(D[0], ln, NoHook{});
+    if constexpr (FB < L) {
+      fft_forward<F, FB, 0>(D[1], ln, [&](auto h) {
+        constexpr int H = decltype(h)::value, HN = F::FWD_HOOKS;
+        static_for<FB * H / HN, FB * (H + 1) / HN>(group);
+      });
+      static_for<FB, NB * L>(group);
+    } else {
+      static_for<0, NB * L>(group);
+    }
+    u32 top[8];
+    static_for<0, SUMS / NB>([&](auto bc) {
+      constexpr int B = decltype(bc)::value;
+      cd(&y)[NB][4] = Y[B & 1];
+      // (NB sums leave room for one set of words: a barrier opens it again)
+      constexpr bool ONE = NB > 1;
+      constexpr int O1 = F::ODD || ONE ? 0 : (B & 1) * C, O2 = ONE ? 0 : C;
+      fft_inverse<F, NB, 0, O1, O2, ONE && (B > 0)>(y, ln, [&](auto h) {
+        if constexpr (B + 1 < SUMS / NB) {
+          constexpr int H = decltype(h)::value, HN = F::INV_HOOKS, M = NB * L;
+          static_for<(B + 1) * M + M * H / HN, (B + 1) * M + M * (H + 1) / HN>(group);
+        }
+      });
+      static_for<0, NB>([&](auto jc) {
+        constexpr int j = decltype(jc)::value, S = B * NB + j, c = S / P, p = S % P;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          add_piece<P, p>(acc[c][k], top[k], y[j][k].re);
+          add_piece<P, p>(acc[c][k + 4], top[k + 4], y[j][k].im);
+        }
+        if constexpr (p == P - 1) {
+#pragma unroll
+          for (int k = 0; k < 8; ++k) acc[c][k] = finish_pieces(acc[c][k], top[k]);
+        }
+      });
+    });
+  }
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int k = 0; k < 8; ++k) out[(ct * 2 + c) * N + tid + T * k] = acc[c][k];
+}
+
+// ---------------------------------------------------------------------------
 // Launch
 // ---------------------------------------------------------------------------
 
@@ -456,6 +629,12 @@ hipError_t allow_lds(K kernel, size_t bytes) {
                              (int)bytes);
 }
 
+// One workgroup per step shares the tables among its 2R rows; few steps take
+// one per row.
+dim3 expand_grid(unsigned steps, unsigned R) {
+  return dim3(steps, steps < (unsigned)device_cus() ? 2 * R : 1);
+}
+
 template <class S, class F, int L, int P, typename RT>
 hipError_t launch_fft(const uint64_t *lwe_in, const uint64_t *bsk_dev, const uint64_t *lut,
                       uint64_t *out, size_t batch, const rosetta_params &p, const Tables &tb,
@@ -464,8 +643,8 @@ hipError_t launch_fft(const uint64_t *lwe_in, const uint64_t *bsk_dev, const uin
   const size_t lds = br_fft_lds_bytes<F, L>((int)p.n);
   hipError_t e;
   if ((e = allow_lds(k_expand_key<S, F, P>, xlds)) != hipSuccess) return e;
-  hipLaunchKernelGGL((k_expand_key<S, F, P>), dim3(p.n), dim3(S::T), xlds, st, bsk_dev, key, L,
-                     tb.zeta, (const cd *)tb.fft);
+  hipLaunchKernelGGL((k_expand_key<S, F, P>), expand_grid(p.n, 2 * L), dim3(S::T), xlds, st, bsk_dev, key,
+                     2 * L, 1.0 / F::C, tb.zeta, (const cd *)tb.fft);
   if ((e = allow_lds(k_blind_rotate_fft<F, L, P, RT>, lds)) != hipSuccess) return e;
   hipLaunchKernelGGL((k_blind_rotate_fft<F, L, P, RT>), dim3(batch), dim3(F::T), lds, st, lwe_in,
                      key, lut, out, (int)p.n, (int)p.pbs_base_log, mode, tp_glwe,
@@ -497,6 +676,44 @@ hipError_t launch_fft_levels(const uint64_t *lwe_in, const uint64_t *bsk_dev, co
   }
 }
 
+template <int LOGN, int L, int P>
+hipError_t launch_trace_fft(const uint64_t *in, const uint64_t *autk_dev, uint64_t *out,
+                            size_t batch, int base_log, const Tables &tb, cd *key,
+                            hipStream_t st) {
+  using S = Ntt<LOGN, ntt_le(LOGN), ntt_first(LOGN)>;
+  using F = Fft<LOGN>;
+  const size_t xlds = F::TABLE_BYTES + (size_t)(S::TW_WORDS + S::XCHG_WORDS) * 8;
+  const size_t lds = trace_fft_lds_bytes<F, L>();
+  hipError_t e;
+  if ((e = allow_lds(k_expand_key<S, F, P>, xlds)) != hipSuccess) return e;
+  if ((e = allow_lds(k_trace_fft<F, L, P>, lds)) != hipSuccess) return e;
+  hipLaunchKernelGGL((k_expand_key<S, F, P>), expand_grid(LOGN, L), dim3(S::T), xlds, st, autk_dev, key, L,
+                     -1.0 / F::C, tb.zeta, (const cd *)tb.fft);
+  hipLaunchKernelGGL((k_trace_fft<F, L, P>), dim3(batch), dim3(F::T), lds, st, in, key, out,
+                     base_log, tb.ninv, (const cd *)tb.fft);
+  return hipGetLastError();
+}
+
+template <int LOGN, int L>
+hipError_t launch_trace_pieces(const uint64_t *in, const uint64_t *autk_dev, uint64_t *out,
+                               size_t batch, int base_log, int pieces, const Tables &tb, cd *key,
+                               hipStream_t st) {
+  return pieces == 3 ? launch_trace_fft<LOGN, L, 3>(in, autk_dev, out, batch, base_log, tb, key, st)
+                     : launch_trace_fft<LOGN, L, 4>(in, autk_dev, out, batch, base_log, tb, key, st);
+}
+
+template <int LOGN>
+hipError_t launch_trace_levels(const uint64_t *in, const uint64_t *autk_dev, uint64_t *out,
+                               size_t batch, int level, int base_log, int pieces,
+                               const Tables &tb, cd *key, hipStream_t st) {
+  switch (level) {
+    case 1: return launch_trace_pieces<LOGN, 1>(in, autk_dev, out, batch, base_log, pieces, tb, key, st);
+    case 2: return launch_trace_pieces<LOGN, 2>(in, autk_dev, out, batch, base_log, pieces, tb, key, st);
+    case 3: return launch_trace_pieces<LOGN, 3>(in, autk_dev, out, batch, base_log, pieces, tb, key, st);
+    default: return launch_trace_pieces<LOGN, 4>(in, autk_dev, out, batch, base_log, pieces, tb, key, st);
+  }
+}
+
 }  // namespace
 
 hipError_t launch_blind_rotate(const uint64_t *lwe_in, const uint64_t *bsk_dev,
@@ -520,6 +737,24 @@ hipError_t launch_blind_rotate(const uint64_t *lwe_in, const uint64_t *bsk_dev,
     // the modular transforms need no expanded key
   }
   return launch_blind_rotate_ntt(lwe_in, bsk_dev, lut, out, batch, p, tb, mode, tp_glwe, st);
+}
+
+hipError_t launch_trace(const uint64_t *in, const uint64_t *autk_dev, uint64_t *out,
+                        size_t batch, uint32_t N, int level, int base_log, const Tables &tb,
+                        hipStream_t st) {
+  const int pieces = fft_pieces_for(N, level, base_log);
+  if (pieces) {
+    const size_t rounds = N == 2048 ? 11 : 12;
+    if (void *key = scratch_take(rounds * 2 * pieces * level * (N / 2) * sizeof(cd), st)) {
+      const hipError_t e = N == 2048 ? launch_trace_levels<11>(in, autk_dev, out, batch, level,
+                                                               base_log, pieces, tb, (cd *)key, st)
+                                     : launch_trace_levels<12>(in, autk_dev, out, batch, level,
+                                                               base_log, pieces, tb, (cd *)key, st);
+      const hipError_t f = scratch_give(key, st);
+      return e != hipSuccess ? e : f;
+    }
+  }
+  return launch_trace_ntt(in, autk_dev, out, batch, N, level, base_log, tb, st);
 }
 
 }  // namespace rosetta

@@ -354,62 +354,105 @@ __device__ __forceinline__ void fft_forward(cd (&x)[NB][4], const Lane &ln, cons
   for (int b = 0; b < NB; ++b) fft_fwd4(x[b], w.a, w.b);
 }
 
-// The inverse transform (times C): slot bits (1,0) in, natural layout out.
-// It works in the wave's own block of words [O1, O1 + C) of the buffer,
-// which nobody else may read any more, writes it once more, and reads all of
-// those words after a barrier; for odd LOGC a second exchange goes through
-// words [O2, O2 + C), which have to be free once that barrier is passed.
-template <class F, int TAB, int O1, int O2, class Lane, class Hook>
-__device__ __forceinline__ void fft_inverse(cd (&x)[4], const Lane &ln, const Hook &hook) {
-  constexpr int H0 = F::ODD ? 6 : 4;
-  auto pass = [&](int at, int bits, int pos16) {
-    const cd a = fft_get(pos16, TAB + 16 * at), v = fft_get(pos16, TAB + 16 * (at + (1 << bits)));
-    fft_inv4(x, a, v);
+// NB inverse transforms (times C) side by side: slot bits (1,0) in, natural
+// layout out.  They work in the wave's own blocks of words [O1, O1 + NB C) of
+// the buffer, which nobody else may read any more (OPEN: a barrier first sees
+// to that), write those once more, and read all of them after a barrier; for
+// odd LOGC a second exchange goes through words [O2, O2 + NB C), which, unless
+// they are the same, have to be free once that barrier is passed.
+template <class F, int NB, int TAB, int O1, int O2, bool OPEN, class Lane, class Hook>
+__device__ __forceinline__ void fft_inverse(cd (&x)[NB][4], const Lane &ln, const Hook &hook) {
+  constexpr int H0 = F::ODD ? 6 : 4, C = F::C;
+  struct Tw {
+    cd a, v;
   };
-  fft_inv4_first(x);
-  wave_sync();
-  FftWords<2, false>(ln).put(x, O1);
-  wave_sync();
-  FftWords<2, true>(ln).get(x, O1);
-  hook(std::integral_constant<int, 0>{});
-  pass(F::inv_at(2), 2, fft_and(ln.t16, 48));
-  wave_sync();
-  FftWords<1, false>(ln).put(x, O1);
-  wave_sync();
-  FftWords<1, true>(ln).get(x, O1);
-  hook(std::integral_constant<int, 1>{});
-  pass(F::inv_at(4), 4, fft_and(ln.t16, 240));
-  fft_lane_swap(x);
-  pass(F::inv_at(6), 6, fft_and(ln.t16, 1008));
-  wave_sync();
-  fft_put_cross<F, 2>(x, O1, ln);
+  auto twiddles = [&](int at, int bits, int pos16) {
+    return Tw{fft_get(pos16, TAB + 16 * at), fft_get(pos16, TAB + 16 * (at + (1 << bits)))};
+  };
+  fft_inv4_first(x[0]);
+  if constexpr (OPEN) __syncthreads();
+  {
+    const FftWords<2, false> lo(ln);
+    const FftWords<2, true> up(ln);
+    static_for<0, NB>([&](auto bc) {
+      constexpr int b = decltype(bc)::value;
+      if constexpr (b > 0) fft_inv4_first(x[b]);
+      lo.put(x[b], O1 + b * C);
+    });
+    const Tw w = twiddles(F::inv_at(2), 2, fft_and(ln.t16, 48));
+    wave_sync();
+#pragma unroll
+    for (int b = 0; b < NB; ++b) up.get(x[b], O1 + b * C);
+    hook(std::integral_constant<int, 0>{});
+    const FftWords<1, false> lo1(ln);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      fft_inv4(x[b], w.a, w.v);
+      lo1.put(x[b], O1 + b * C);
+    }
+  }
+  {
+    const FftWords<1, true> up(ln);
+    const Tw w = twiddles(F::inv_at(4), 4, fft_and(ln.t16, 240));
+    wave_sync();
+#pragma unroll
+    for (int b = 0; b < NB; ++b) up.get(x[b], O1 + b * C);
+    hook(std::integral_constant<int, 1>{});
+    const Tw v = twiddles(F::inv_at(6), 6, fft_and(ln.t16, 1008));
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      fft_inv4(x[b], w.a, w.v);
+      fft_lane_swap(x[b]);
+      fft_inv4(x[b], v.a, v.v);
+      fft_put_cross<F, 2>(x[b], O1 + b * C, ln);
+    }
+  }
   hook(std::integral_constant<int, 2>{});
   __syncthreads();
   if constexpr (F::ODD) {
-    fft_get_cross<F, 1>(x, O1, ln);
+    const Tw w = twiddles(F::inv_at(8), 8, fft_and(ln.t16, 4080));
+#pragma unroll
+    for (int b = 0; b < NB; ++b) fft_get_cross<F, 1>(x[b], O1 + b * C, ln);
     hook(std::integral_constant<int, 3>{});
-    pass(F::inv_at(8), 8, fft_and(ln.t16, 4080));
-    fft_put_cross<F, 1>(x, O2, ln);
+    fft_inv4(x[0], w.a, w.v);
+    if constexpr (O1 == O2) __syncthreads();
+    static_for<0, NB>([&](auto bc) {
+      constexpr int b = decltype(bc)::value;
+      if constexpr (b > 0) fft_inv4(x[b], w.a, w.v);
+      fft_put_cross<F, 1>(x[b], O2 + b * C, ln);
+    });
     hook(std::integral_constant<int, 4>{});
     __syncthreads();
-    fft_get_cross<F, 0>(x, O2, ln);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) fft_get_cross<F, 0>(x[b], O2 + b * C, ln);
   } else {
-    fft_get_cross<F, 0>(x, O1, ln);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) fft_get_cross<F, 0>(x[b], O1 + b * C, ln);
   }
   hook(std::integral_constant<int, H0 - 1>{});
   if constexpr (F::ODD) {
     const cd w = fft_get(ln.t16, TAB + 16 * F::LAST_AT);
-    fft_bfly(x[0], x[2], w.re, w.im);
-    fft_bfly(x[1], x[3], w.im, -w.re);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      fft_bfly(x[b][0], x[b][2], w.re, w.im);
+      fft_bfly(x[b][1], x[b][3], w.im, -w.re);
+    }
   } else {
-    pass(F::inv_at(8), 8, ln.t16);
+    const Tw w = twiddles(F::inv_at(8), 8, ln.t16);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) fft_inv4(x[b], w.a, w.v);
   }
   // e(-(t + T k) / 4C) = e(-t / 4C) e(-k / 16)
   const cd w0 = fft_get(ln.t16, TAB + 16 * F::TWIST_AT);
-  x[0] = fft_mul(x[0], w0);
-  x[1] = fft_mul(x[1], fft_mul(w0, cd{FFT_C16, -FFT_S16}));
-  x[2] = fft_mul(x[2], fft_mul(w0, cd{FFT_C8, -FFT_C8}));
-  x[3] = fft_mul(x[3], fft_mul(w0, cd{FFT_S16, -FFT_C16}));
+  const cd w1 = fft_mul(w0, cd{FFT_C16, -FFT_S16}), w2 = fft_mul(w0, cd{FFT_C8, -FFT_C8}),
+           w3 = fft_mul(w0, cd{FFT_S16, -FFT_C16});
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    x[b][0] = fft_mul(x[b][0], w0);
+    x[b][1] = fft_mul(x[b][1], w1);
+    x[b][2] = fft_mul(x[b][2], w2);
+    x[b][3] = fft_mul(x[b][3], w3);
+  }
 }
 
 }  // namespace rosetta

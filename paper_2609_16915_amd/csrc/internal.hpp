@@ -76,10 +76,11 @@ void *scratch_take(size_t bytes, hipStream_t st);
 hipError_t scratch_give(void *p, hipStream_t st);
 void scratch_release();
 
-// Pieces per key coefficient of the double-precision blind rotation: 3 of 22
-// bits, 4 of 16, or 0 where only the modular transforms are exact.
+// Pieces per key coefficient of the double-precision blind rotation and
+// trace, R rows of base_log = beta bits: 3 of 22 bits, 4 of 16, or 0 where
+// only the modular transforms are exact.
 //
-// Error bound, u = 2^-53, M = log2(N/2) stages, R = 2l rows.  A butterfly's
+// Error bound, u = 2^-53, M = log2(N/2) stages.  A butterfly's
 // sum is off by at most u(2|a| + 3|b|), its difference by u(3|a| + 4|b|)
 // (inputs a, b; roundings and the twiddle's own u), in the 2-norm 4.4 u of
 // the outputs, so the transforms of a digit polynomial d and of a piece k
@@ -90,25 +91,33 @@ void scratch_release();
 // which is at most sum ||d|| ||k|| (Cauchy-Schwarz and Parseval).  Together
 // 146 u at N = 2048 and 158 u at N = 4096 for R = 6: 160 u.  With |d| <=
 // 2^(beta-1) and |k| <= 2^(b-1), ||d|| ||k|| <= N 2^(beta + b - 2), hence
-//   error <= 2 l N 2^(beta + b - 2) 160 2^-53, wanted <= 1/4.
+//   error <= R N 2^(beta + b - 2) 160 2^-53, wanted <= 1/4.
 // No input can exceed it: the bound holds for every digit and key word.
-inline int fft_pieces(const rosetta_params &p) {
-  if ((p.N != 2048 && p.N != 4096) || p.pbs_level > 3) return 0;
+inline int fft_pieces_for(unsigned N, unsigned rows, unsigned base_log) {
+  if (N != 2048 && N != 4096) return 0;
+  const uint64_t f = (uint64_t)rows * N * 160;  // below 2^24
   auto holds = [&](unsigned bits) {
-    const unsigned e = p.pbs_base_log + bits - 2;
-    return e < 40 && ((uint64_t)2 * p.pbs_level * p.N * 160 << e) >> e ==
-                         (uint64_t)2 * p.pbs_level * p.N * 160 &&
-           (uint64_t)2 * p.pbs_level * p.N * 160 << e <= (uint64_t)1 << 51;
+    const unsigned e = base_log + bits - 2;
+    return e < 40 && f << e <= (uint64_t)1 << 51;
   };
-  if (p.pbs_level * p.pbs_base_log <= 30 && holds(22)) return 3;
-  if (holds(16)) return 4;
-  return 0;
+  return holds(22) ? 3 : holds(16) ? 4 : 0;
 }
+inline int fft_pieces(const rosetta_params &p) {
+  if (p.pbs_level > 3) return 0;  // (no registers for eight transforms)
+  const int pieces = fft_pieces_for(p.N, 2 * p.pbs_level, p.pbs_base_log);
+  // the 3-piece instances keep the rounded value in 32 bits
+  return pieces == 3 && p.pbs_level * p.pbs_base_log > 30 ? 4 : pieces;
+}
+
 hipError_t launch_rows_prepare(const uint64_t *rows_std, uint64_t *rows_dev, size_t rows,
                                uint32_t N, const Tables &tb, hipStream_t st);
+// Trace: as launch_blind_rotate, with double-precision transforms where it can.
 hipError_t launch_trace(const uint64_t *in, const uint64_t *autk_dev, uint64_t *out,
                         size_t batch, uint32_t N, int level, int base_log, const Tables &tb,
                         hipStream_t st);
+hipError_t launch_trace_ntt(const uint64_t *in, const uint64_t *autk_dev, uint64_t *out,
+                            size_t batch, uint32_t N, int level, int base_log, const Tables &tb,
+                            hipStream_t st);
 hipError_t launch_glwe_mul_plain(const uint64_t *in, const uint64_t *pa_dev, const uint64_t *pb,
                                  uint64_t *out, size_t batch, int npoly, uint32_t N,
                                  const Tables &tb, hipStream_t st);

@@ -570,24 +570,6 @@ k_blind_rotate(const u64 *__restrict__ lwe_in, const u64 *__restrict__ bsk,
 // RLWE trace, plaintext products, recombination (lookup protocol)
 // ---------------------------------------------------------------------------
 
-// d^-1 modulo 2N for odd d: Newton's iteration x <- x (2 - d x) doubles the
-// number of correct low bits, starting from x = d (d^2 = 1 mod 8).
-__device__ __forceinline__ u32 odd_inverse_mod(u32 d, u32 two_n) {
-  u32 x = d;
-#pragma unroll
-  for (int it = 0; it < 4; ++it) x *= 2u - d * x;
-  return x & (two_n - 1);
-}
-
-// Coefficient j of tau_d(a) = a(X^d): with e = j d^-1 mod 2N, the source
-// is a_e (e < N) or -a_(e-N) (X^N = -1).  `a` is in natural layout in LDS.
-template <int N>
-__device__ __forceinline__ u64 automorphism_coef(const u64 *a, int j, u32 dinv) {
-  const u32 e = ((u32)j * dinv) & (2 * N - 1);
-  const u64 v = a[e & (N - 1)];
-  return e < (u32)N ? v : gl_neg(v);
-}
-
 // Trace of one GLWE ciphertext per workgroup (the RLWE trace of the lookup
 // protocol): c <- N^-1 c, then for k = log2 N down to 1 with d = 2^k + 1,
 //   c <- c + KS_d(tau_d(c)),
@@ -950,9 +932,9 @@ hipError_t launch_rows_prepare(const uint64_t *rows_std, uint64_t *rows_dev, siz
   return hipGetLastError();
 }
 
-hipError_t launch_trace(const uint64_t *in, const uint64_t *autk_dev, uint64_t *out,
-                        size_t batch, uint32_t N, int level, int base_log, const Tables &tb,
-                        hipStream_t st) {
+hipError_t launch_trace_ntt(const uint64_t *in, const uint64_t *autk_dev, uint64_t *out,
+                            size_t batch, uint32_t N, int level, int base_log, const Tables &tb,
+                            hipStream_t st) {
 #define ROSETTA_TR_L(LV)                                                                 \
   case LV:                                                                               \
     ROSETTA_LAUNCH((k_trace<S, LV>), dim3(batch), dim3(S::T), ntt_lds_bytes<S>(), st, in, \

@@ -773,6 +773,24 @@ __device__ __forceinline__ u64 rotated_coef(const u64 *v, int j, int r) {
   return neg ? gl_neg(x) : x;
 }
 
+// d^-1 modulo 2N for odd d: Newton's iteration x <- x (2 - d x) doubles the
+// number of correct low bits, starting from x = d (d^2 = 1 mod 8).
+__device__ __forceinline__ u32 odd_inverse_mod(u32 d, u32 two_n) {
+  u32 x = d;
+#pragma unroll
+  for (int it = 0; it < 4; ++it) x *= 2u - d * x;
+  return x & (two_n - 1);
+}
+
+// Coefficient j of tau_d(a) = a(X^d): with e = j d^-1 mod 2N, the source
+// is a_e (e < N) or -a_(e-N) (X^N = -1).  `a` is in natural layout in LDS.
+template <int N>
+__device__ __forceinline__ u64 automorphism_coef(const u64 *a, int j, u32 dinv) {
+  const u32 e = ((u32)j * dinv) & (2 * N - 1);
+  const u64 v = a[e & (N - 1)];
+  return e < (u32)N ? v : gl_neg(v);
+}
+
 // Global-address-space view of a device pointer.
 __device__ __forceinline__ gconst_u64 *as_global(const u64 *p) { return (gconst_u64 *)p; }
 

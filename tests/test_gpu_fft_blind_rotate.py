@@ -126,3 +126,33 @@ def test_streams_hold_their_own_expanded_keys():
     R.shutdown()  # gives the pool back; the next call makes it anew
     _, bsk, d_in, _, want = jobs[0]
     assert np.array_equal(R.to_host(R.blind_rotate_extract(d_in, bsk, lut, prm)), want)
+
+
+@pytest.mark.parametrize("N", [2048, 4096])
+@pytest.mark.parametrize("level,base", [(1, 11), (1, 17), (1, 18), (2, 10), (2, 16), (3, 10), (3, 15),
+                                        (4, 9), (4, 12), (4, 15)])
+def test_trace_equals_the_modular_transforms(O, N, level, base):
+    """Traces at the edges of the rule (3 pieces, 4 pieces, none), on extreme
+    words, in place too: against the modular kernel (a captured call) and the
+    oracle."""
+    torch = require_gpu()
+    prm = _params(N, 1, 8, 3)
+    rng = np.random.default_rng(N + 10 * level + base)
+    ak_std = _words(rng, R.autk_words(prm, level))
+    ak = R.autk_prepare(R.to_device(ak_std), prm, level)
+    say(f"[fft trace] N={N} {level}x{base}")
+    for batch in (1, 600):
+        ct = _words(rng, batch, 2 * N)
+        d = R.to_device(ct)
+        got = R.to_host(R.trace(d, ak, prm, level, base))
+        ref = R.empty((batch, 2 * N))
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            R.trace(d, ak, prm, level, base, out=ref)
+        for _ in range(2):
+            graph.replay()
+            torch.cuda.synchronize()
+            assert np.array_equal(got, R.to_host(ref))
+        assert np.array_equal(got, R.to_host(R.trace(d, ak, prm, level, base, out=d)))
+    assert np.array_equal(got[0], O.trace(N, level, base, ct[0], ak_std, O.NTT))
