@@ -566,6 +566,165 @@ k_blind_rotate(const u64 *__restrict__ lwe_in, const u64 *__restrict__ bsk,
   }
 }
 
+// Small rings (N <= 1024), few ciphertexts: 2L teams of T threads on one
+// ciphertext.  k_blind_rotate leaves such a launch one or two waves per CU
+// that transform a step's 2L digit polynomials one after the other; here team
+// r = u L + t takes digit t of component u, transforms it, multiplies it with
+// its two key rows (loaded a step ahead) and leaves the products in LDS; team
+// c then adds up component c's 2L products, takes the sum back and adds it to
+// the accumulator, which lives in LDS.  Bound: the latency of one forward and
+// one inverse transform per step, with the CU mostly waiting; the tiny set
+// (n = 64, N = 256, l = 2), eight ciphertexts: 272 us, 638 us with
+// k_blind_rotate.
+//
+// Dynamic LDS: twiddles [TW_WORDS], accumulator [2N], the teams' exchange
+// buffers [2L][2N] (the products, [2][N], in the same words), rotation amounts.
+constexpr size_t LDS_PER_CU = 160 * 1024;
+
+template <class S, int L>
+constexpr size_t br_teams_lds_bytes(int n) {
+  return (size_t)(S::TW_WORDS + 2 * S::N + 2 * L * S::XCHG_WORDS) * sizeof(u64) +
+         (((size_t)(n + 1) * 2 + 15) & ~(size_t)15);
+}
+
+template <class S, int L, typename RT>
+__global__ void __launch_bounds__(2 * L * S::T)
+k_blind_rotate_teams(const u64 *__restrict__ lwe_in, const u64 *__restrict__ bsk,
+                     const u64 *__restrict__ lut, u64 *__restrict__ out, int n, int beta, int mode,
+                     int tp_glwe, const u64 *__restrict__ zeta) {
+  constexpr int N = S::N, E = S::E, T = S::T, TEAMS = 2 * L;
+  static_assert(T % 64 == 0 && S::XCHG_WORDS == 2 * N, "whole waves, room for the products");
+  constexpr bool ONE_WAVE = T == 64;  // the transforms hold no workgroup barrier
+  u64 *tw = lds_dyn;
+  u64 *acc = lds_dyn + S::TW_WORDS;
+  u64 *regions = acc + 2 * N;
+  uint16_t *rot = (uint16_t *)(regions + TEAMS * 2 * N);
+  const int tid = threadIdx.x % T;
+  const int r = __builtin_amdgcn_readfirstlane(threadIdx.x / T);
+  const int u = r / L, t = r % L;
+  u64 *own = regions + r * 2 * N;
+  LdsBufs<S> lds(own);
+  const size_t ct = blockIdx.x;
+
+  const u64 *lwe = lwe_in + (ct / (size_t)(tp_glwe > 1 ? tp_glwe : 1)) * (size_t)(n + 1);
+  for (int i = threadIdx.x; i <= n; i += TEAMS * T)
+    rot[i] = (uint16_t)gl_modswitch(lwe[i], S::LOGN);
+  for (int i = threadIdx.x; i < S::TW_WORDS; i += TEAMS * T) tw[i] = zeta[i];
+  __syncthreads();
+  if (r < 2) {
+    const int a = (2 * N - (int)rot[n]) & (2 * N - 1);  // X^(-b~)
+    const u64 *tp = lut + (tp_glwe ? (ct * 2 + r) * (size_t)N : 0);
+#pragma unroll
+    for (int k = 0; k < E; ++k)
+      acc[r * N + tid + T * k] = tp_glwe || r ? rotated_coef<N>(tp, tid + T * k, a) : 0;
+  }
+
+  const int s = 64 - L * beta;
+  const RT half = (RT)1 << (beta - 1);
+  const int dsh = (int)(8 * sizeof(RT)) - beta;
+  const u64 *g = bsk + (size_t)r * 2 * N + tid;  // this team's two rows of GGSW_0
+  constexpr size_t ggsw_words = (size_t)TEAMS * 2 * N;
+  u64 g0[E], g1[E];
+#pragma unroll
+  for (int k = 0; k < E; ++k) {
+    g0[k] = g[k * T];
+    g1[k] = g[N + k * T];
+  }
+#pragma unroll 1
+  for (int i = 0; i < n; ++i) {
+    __syncthreads();  // the accumulator is whole
+    const int a = __builtin_amdgcn_readfirstlane(rot[i]);
+    const int ar = a & (N - 1);
+    const bool flip = a >= N;
+    RT d[E];
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
+      const int j = tid + T * k;
+      const bool neg = (j < ar) != flip;
+      const u64 v = acc[u * N + ((j - ar) & (N - 1))];
+      const u64 x = gl_sub(neg ? GL_P - v : v, acc[u * N + j]);
+      if constexpr (sizeof(RT) == 4)
+        d[k] = gl_round_top32(x, s);
+      else
+        d[k] = gl_round_top(x, s);
+    }
+    // digit t: the levels below it carried up first
+    for (int q = L - 1; q > t; --q)
+#pragma unroll
+      for (int k = 0; k < E; ++k) d[k] = (d[k] + half) >> beta;
+    if (t > 0)
+#pragma unroll
+      for (int k = 0; k < E; ++k) d[k] = (RT)((std::make_unsigned_t<RT>)d[k] << dsh) >> dsh;
+    u64 x[E];
+    if (beta <= 14) {
+      ntt_forward_small<S, RT>(d, x, lds, tid, tw);
+    } else {
+#pragma unroll
+      for (int k = 0; k < E; ++k) x[k] = gl_from_i64((i64)d[k]);
+      ntt_forward<S>(x, lds, tid, tw);
+    }
+    // the team's exchange words are free once the team has read them
+    if constexpr (ONE_WAVE)
+      wave_sync();
+    else
+      __syncthreads();
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
+      own[k * T + tid] = gl_mul(x[k], g0[k]);
+      own[N + k * T + tid] = gl_mul(x[k], g1[k]);
+    }
+    if (i + 1 < n) {
+      const u64 *gn = g + (size_t)(i + 1) * ggsw_words;
+#pragma unroll
+      for (int k = 0; k < E; ++k) {
+        g0[k] = gn[k * T];
+        g1[k] = gn[N + k * T];
+      }
+    }
+    __syncthreads();
+    // component c: every team where the transform holds barriers, else two
+    const int c = r & 1;
+    u64 y[E];
+    if (!ONE_WAVE || r < 2) {
+#pragma unroll
+      for (int k = 0; k < E; ++k) y[k] = regions[c * N + k * T + tid];
+#pragma unroll
+      for (int q = 1; q < TEAMS; ++q)
+#pragma unroll
+        for (int k = 0; k < E; ++k) y[k] = gl_add(y[k], regions[(q * 2 + c) * N + k * T + tid]);
+    }
+    __syncthreads();
+    if (!ONE_WAVE || r < 2) {
+      ntt_inverse<S>(y, lds, tid, tw);
+      if (r < 2) {
+#pragma unroll
+        for (int k = 0; k < E; ++k) {
+          u64 &w = acc[c * N + tid + T * k];
+          w = gl_add(w, y[k]);
+        }
+      }
+    }
+  }
+  __syncthreads();
+
+  if (r >= 2) return;
+  if (mode == BR_GLWE) {
+    u64 *o = out + (ct * 2 + r) * (size_t)N;
+#pragma unroll
+    for (int k = 0; k < E; ++k) o[tid + T * k] = acc[r * N + tid + T * k];
+  } else {
+    u64 *o = out + ct * (size_t)(N + 1);
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
+      const int j = tid + T * k;
+      if (r == 0)
+        o[(N - j) & (N - 1)] = j ? gl_neg(acc[j]) : acc[j];
+      else if (j == 0)
+        o[N] = acc[N];
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // RLWE trace, plaintext products, recombination (lookup protocol)
 // ---------------------------------------------------------------------------
@@ -897,6 +1056,25 @@ static hipError_t launch_br_levels(const uint64_t *lwe_in, const uint64_t *bsk_d
   if constexpr (S::LOGN >= 12) {
     if (batch <= (size_t)device_cus()) {
       ROSETTA_BR_INST(2);
+      return hipSuccess;
+    }
+  }
+  // Small rings, up to two ciphertexts per CU: the teams kernel.  512
+  // ciphertexts at n = 64, teams against k_blind_rotate: N = 256, l = 1/2/4
+  // 326/331/512 us against 503/682/1294; N = 512, l = 3 1.11 ms against 1.57;
+  // N = 1024, l = 1/2/4 0.37/1.48/2.55 ms (n = 33/64/64) against
+  // 0.64/1.85/3.04.  With 768 the larger rings are slower in teams (1.67 ms
+  // against 1.54 at N = 512, l = 3).  A very large n leaves no room for the
+  // rotation amounts beside the products at N = 1024, l = 4.
+  if constexpr (S::LOGN <= 10) {
+    const size_t tlds = br_teams_lds_bytes<S, L>(n);
+    if (batch <= 2 * (size_t)device_cus() && tlds <= LDS_PER_CU) {
+      if (L * beta <= 30)
+        ROSETTA_LAUNCH((k_blind_rotate_teams<S, L, int32_t>), dim3(batch), dim3(2 * L * S::T), tlds,
+                       st, lwe_in, bsk_dev, lut, out, n, beta, mode, tp_glwe, tb.zeta);
+      else
+        ROSETTA_LAUNCH((k_blind_rotate_teams<S, L, int64_t>), dim3(batch), dim3(2 * L * S::T), tlds,
+                       st, lwe_in, bsk_dev, lut, out, n, beta, mode, tp_glwe, tb.zeta);
       return hipSuccess;
     }
   }
