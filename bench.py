@@ -42,14 +42,17 @@ CU, CLOCK_HZ, LANES = 256, 2.4e9, 64
 MODMUL_VALU_OPS = 17
 MODMUL_PEAK_T = CU * CLOCK_HZ * LANES / MODMUL_VALU_OPS / 1e12   # Tmodmul/s
 MULTIPLIER_BOUND_T = CU * CLOCK_HZ * LANES / 4 / 1e12
+# Double precision: one fused multiply-add per lane and clock, as any other
+# full-rate instruction: 78.6 TFLOP/s.
+FP64_PEAK_T = 2 * CU * CLOCK_HZ * LANES / 1e12
 INT8_PEAK_P = 5.0   # MI355X dense int8 matrix-core peak, POP/s (no sparsity)
-PMC_PROFILE = os.path.join(ROOT, "profiles", "k_blind_rotate_llama3_8b_silu_pmc.md")
-KERNEL_SOURCES = ["gl.hpp", "ntt.hpp", "kernels.hip"]
+PMC_PROFILE = os.path.join(ROOT, "profiles", "k_blind_rotate_fft_llama3_8b_silu_pmc.md")
+KERNEL_SOURCES = ["gl.hpp", "ntt.hpp", "fft.hpp", "exact_fft.hip"]
 
 
 def kernel_source_digest() -> str:
-    """sha256 of the blind-rotation kernel sources (gl.hpp, ntt.hpp,
-    kernels.hip in that order) with comments and whitespace removed, so that
+    """sha256 of the sources of the headline's blind-rotation kernel (gl.hpp,
+    ntt.hpp, fft.hpp, exact_fft.hip in that order) with comments and whitespace removed, so that
     it changes with the code and not with its prose."""
     import hashlib
     import re
@@ -80,6 +83,28 @@ def measured_traffic(workload: str, batch: int):
     if not m_sha or not m_tb or m_sha.group(1) != kernel_source_digest():
         return None
     return float(m_tb.group(1))
+
+
+def key_pieces(N: int, level: int, base_log: int) -> int:
+    """Pieces the key is cut into for double-precision transforms (the rule
+    of fft_pieces in csrc/internal.hpp), 0 where the modular ones run."""
+    if N not in (2048, 4096) or level > 3:
+        return 0
+
+    def holds(bits):
+        return 2 * level * N * 160 << (base_log + bits - 2) <= 1 << 51
+
+    if level * base_log <= 30 and holds(22):
+        return 3
+    return 4 if holds(16) else 0
+
+
+def fft_flops(N: int, log_bfly: int, forward: int, inverse: int, products: int) -> int:
+    """Double-precision operations (a fused multiply-add is two) of complex
+    transforms of N/2 points, six multiply-adds per butterfly, and of complex
+    products summed up, four per point."""
+    C = N // 2
+    return 2 * (6 * (C // 2) * log_bfly * (forward + inverse) + 4 * C * products)
 
 
 def modmul_probe(stream, reps: int = 5) -> float:
@@ -197,15 +222,18 @@ def lookup_select(R, W, w, p, keys, d_in, bsk, stream, steps):
     wall = (time.perf_counter() - t0) / steps
     br_ms = float(np.mean([a.elapsed_time(b) for a, b, _ in ev]))
     tr_ms = float(np.mean([b.elapsed_time(c) for _, b, c in ev]))
-    tr_mm = w.trace_modmul(TRACE_LEVEL) * w.batch
-    tr_t = tr_mm / (tr_ms * 1e-3) / 1e12
+    # (the trace's key is in 4 pieces at these parameters: log2 N rounds of
+    # TRACE_LEVEL forward and 2 x 4 inverse transforms)
+    rounds = int(math.log2(w.N))
+    tr_flops = w.batch * rounds * fft_flops(w.N, rounds - 1, TRACE_LEVEL, 8, 8 * TRACE_LEVEL)
+    tr_t = tr_flops / (tr_ms * 1e-3) / 1e12
     return {"batch": w.batch, "trace_level": TRACE_LEVEL, "trace_base_log": TRACE_BASE_LOG,
             "selects_per_s": round(w.batch / wall, 2), "ms_per_step": round(wall * 1e3, 3),
             "kernels_ms": {"blind_rotate_glwe": round(br_ms, 3), "trace": round(tr_ms, 3)},
-            "roofline_trace": {"bound": "alu", "kernel": "k_trace",
-                               "achieved": round(tr_t, 4), "peak": round(MODMUL_PEAK_T, 4),
-                               "unit": "Tmodmul/s", "frac": round(tr_t / MODMUL_PEAK_T, 4),
-                               "per_launch_modmul": tr_mm, "launch_ms": round(tr_ms, 3)}}
+            "roofline_trace": {"bound": "alu", "kernel": "k_trace_fft", "dtype": "f64",
+                               "achieved": round(tr_t, 4), "peak": round(FP64_PEAK_T, 4),
+                               "unit": "TFLOP/s", "frac": round(tr_t / FP64_PEAK_T, 4),
+                               "per_launch_flops": tr_flops, "launch_ms": round(tr_ms, 3)}}
 
 
 def lookup_protocol(R, W, stream, steps, batch):
@@ -538,15 +566,30 @@ def main():
     modmul_per_launch = w.br_modmul_per_pbs() * w.batch
     achieved_t = modmul_per_launch / (br_ms * 1e-3) / 1e12
     probe_t = modmul_probe(stream)
-    roofline = {"bound": "alu", "kernel": "k_blind_rotate", "achieved": round(achieved_t, 4),
-                "peak": round(MODMUL_PEAK_T, 4), "unit": "Tmodmul/s",
-                "frac": round(achieved_t / MODMUL_PEAK_T, 4),
-                "traffic": measured_traffic(name, w.batch),
-                "per_launch_modmul": modmul_per_launch, "launch_ms": round(br_ms, 3),
-                "multiplier_bound": round(MULTIPLIER_BOUND_T, 4),
-                "frac_of_multiplier_bound": round(achieved_t / MULTIPLIER_BOUND_T, 4),
-                "modmul_probe": round(probe_t, 4),
-                "frac_of_modmul_probe": round(achieved_t / probe_t, 4)}
+    pieces = key_pieces(w.N, w.pbs_level, w.pbs_base_log)
+    if pieces:
+        # double-precision transforms take the modular products' place, so the
+        # modular count is an equivalent (its frac may pass 1) and the roofline
+        # counts the double-precision operations the method needs
+        flops = w.batch * w.n * fft_flops(w.N, int(math.log2(w.N)) - 1, 2 * w.pbs_level,
+                                          2 * pieces, 4 * w.pbs_level * pieces)
+        achieved_f = flops / (br_ms * 1e-3) / 1e12
+        roofline = {"bound": "alu", "kernel": "k_blind_rotate_fft", "dtype": "f64",
+                    "achieved": round(achieved_f, 4), "peak": round(FP64_PEAK_T, 4),
+                    "unit": "TFLOP/s", "frac": round(achieved_f / FP64_PEAK_T, 4),
+                    "traffic": measured_traffic(name, w.batch),
+                    "per_launch_flops": flops, "key_pieces": pieces}
+    else:
+        roofline = {"bound": "alu", "kernel": "k_blind_rotate", "achieved": round(achieved_t, 4),
+                    "peak": round(MODMUL_PEAK_T, 4), "unit": "Tmodmul/s",
+                    "frac": round(achieved_t / MODMUL_PEAK_T, 4),
+                    "traffic": measured_traffic(name, w.batch)}
+    roofline.update({"launch_ms": round(br_ms, 3), "per_launch_modmul": modmul_per_launch,
+                     "modmul_equivalent": round(achieved_t, 4),
+                     "modmul_peak": round(MODMUL_PEAK_T, 4),
+                     "modmul_equivalent_frac": round(achieved_t / MODMUL_PEAK_T, 4),
+                     "multiplier_bound": round(MULTIPLIER_BOUND_T, 4),
+                     "modmul_probe": round(probe_t, 4)})
     hbm_bytes = (w.bsk_words() + w.ksk_words()) * 8 + w.batch * 2 * (w.n + 1) * 8 + w.N * 8
     # the key switch on the int8 matrix cores (the condition rosetta.h states
     # for its byte-plane key): 8 byte-plane products of 2 ops per digit MAC
@@ -556,7 +599,7 @@ def main():
     # executes 8 byte-plane products per MAC (dense_equivalent_ops)
     ks_ops = 2 * w.batch * w.N * w.ks_level * (w.n + 1)
     ks_dense = 8 * ks_ops
-    roofline_ks = ({"bound": "mfma", "kernel": "k_keyswitch_mfma", "dtype": "i8",
+    roofline_ks = ({"bound": "mfma", "kernel": "k_keyswitch_gemm", "dtype": "i8",
                     "achieved": round(ks_ops / (ks_ms * 1e-3) / 1e15, 5),
                     "peak": INT8_PEAK_P, "unit": "POP/s",
                     "frac": round(ks_ops / (ks_ms * 1e-3) / 1e15 / INT8_PEAK_P, 5),

@@ -165,7 +165,9 @@ rosetta_status rosetta_ksk_prepare(const uint64_t *ksk_std_dev, uint64_t *ksk_de
  * keeps at most 4 GiB per device between calls and is given back by
  * rosetta_shutdown().  Where that memory is not to be had, and while the
  * stream is being captured, the modular transforms run instead, with the
- * same output bits. */
+ * same output bits.  rosetta_trace expands its key, and the key switch of a
+ * large batch keeps the digits of its ciphertexts (at most 512 MiB at a time),
+ * in that memory in the same way. */
 rosetta_status rosetta_pbs_batch(const uint64_t *lwe_in, const uint64_t *bsk_dev,
                                  const uint64_t *ksk_dev, const uint64_t *lut, uint64_t *lwe_out,
                                  size_t batch, const rosetta_params *params, void *stream);
@@ -185,7 +187,8 @@ rosetta_status rosetta_pbs_batch_ws(const uint64_t *lwe_in, const uint64_t *bsk_
  * memory while they run: code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc.  Same arguments, layouts, validation and
  * output bits as rosetta_pbs_batch (its blind rotation always runs the
- * modular transforms, which need no expanded key); the scratch
+ * modular transforms, which need no expanded key, and its key switch makes
+ * the digits where it uses them); the scratch
  * between them (the extracted ciphertexts, rosetta_pbs_workspace_bytes
  * bytes) is a static device array of ROSETTA_NOALLOC_SCRATCH_BYTES that
  * each GPU the library runs on holds until the process ends, and the

@@ -226,7 +226,7 @@ constexpr size_t br_fft_lds_bytes(int n) {
 // component 1's, the groups of sum S + 1 during sum S's inverse.
 //
 // Bound: VALU issue.  N = 2048, l = 3: 3.3k VALU instructions per wave and
-// step (9.3k with modular transforms), 1536 ciphertexts 64.8 ms against 96
+// step (9.3k with modular transforms), 1536 ciphertexts 62.0 ms against 96
 // ms; two workgroups share a CU (77 KB of LDS, 256 registers) and keep the
 // VALU about three quarters busy; without the key loads (a build that
 // computes something else) the step is 20 % shorter, with all keys in the L2
