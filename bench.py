@@ -580,7 +580,9 @@ def main():
                     "traffic": measured_traffic(name, w.batch),
                     "per_launch_flops": flops, "key_pieces": pieces}
     else:
-        roofline = {"bound": "alu", "kernel": "k_blind_rotate", "achieved": round(achieved_t, 4),
+        few = w.N <= 1024 and w.batch <= 2 * CU
+        roofline = {"bound": "alu", "kernel": "k_blind_rotate_teams" if few else "k_blind_rotate",
+                    "achieved": round(achieved_t, 4),
                     "peak": round(MODMUL_PEAK_T, 4), "unit": "Tmodmul/s",
                     "frac": round(achieved_t / MODMUL_PEAK_T, 4),
                     "traffic": measured_traffic(name, w.batch)}
