@@ -70,8 +70,8 @@ hipError_t launch_blind_rotate_ntt(const uint64_t *lwe_in, const uint64_t *bsk_d
                                    int tp_glwe, hipStream_t st);
 // Device memory for one call on stream st (scratch.cpp): nullptr where it is
 // not to be had, the stream being captured included.  scratch_give returns it
-// once the work enqueued so far is done; scratch_release gives what the pools
-// keep back to the devices.
+// once the work enqueued so far is done; scratch_release waits for every
+// device that has a pool and gives what the pools keep back to it.
 void *scratch_take(size_t bytes, hipStream_t st);
 hipError_t scratch_give(void *p, hipStream_t st);
 void scratch_release();

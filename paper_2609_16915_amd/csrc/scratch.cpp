@@ -56,9 +56,19 @@ void *scratch_take(size_t bytes, hipStream_t st) {
 
 hipError_t scratch_give(void *p, hipStream_t st) { return hipFreeAsync(p, st); }
 
+// Frees still pending on a stream are not the pool's to give back yet, and a
+// device may have a pool and no other state of the library (a program that
+// only key-switches), so each device is waited for here.
 void scratch_release() {
+  int cur = 0;
+  (void)hipGetDevice(&cur);
   std::lock_guard<std::mutex> lock(g_mu);
-  for (auto &kv : g_pools) (void)hipMemPoolTrimTo(kv.second, 0);
+  for (auto &kv : g_pools) {
+    (void)hipSetDevice(kv.first);
+    (void)hipDeviceSynchronize();
+    (void)hipMemPoolTrimTo(kv.second, 0);
+  }
+  (void)hipSetDevice(cur);
 }
 
 }  // namespace rosetta

@@ -1,0 +1,48 @@
+"""The memory that calls take for themselves (stream-ordered, from one pool per
+device): what is given back, and when."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+from gpu_helpers import require_gpu, say
+
+pytestmark = pytest.mark.gpu
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+ONLY_KEY_SWITCHES = """
+import time
+
+import torch
+from paper_2609_16915_amd import rosetta as R
+prm = dict(n=1024, k=1, N=2048, pbs_level=3, pbs_base_log=8, ks_level=6, ks_base_log=3, msg_bits=6)
+ksk = R.ksk_prepare(torch.zeros(R.ksk_words(prm), dtype=torch.int64, device="cuda"), prm)
+big = torch.zeros((14336, 2049), dtype=torch.int64, device="cuda")
+out = R.empty((14336, 1025))
+R.keyswitch(big[:1].contiguous(), ksk, prm)
+torch.cuda.synchronize()
+before = torch.cuda.mem_get_info()[0]
+for _ in range(8):
+    R.keyswitch(big, ksk, prm, out=out)
+R.shutdown()  # with the key switches still running
+torch.cuda.synchronize()
+for _ in range(20):  # the device's count of free memory lags a little
+    time.sleep(0.1)
+    held = before - torch.cuda.mem_get_info()[0]
+    if held < 32 << 20:
+        break
+print("HELD", held, flush=True)
+"""
+
+
+def test_shutdown_gives_back_what_key_switches_took():
+    """In a process of its own, which calls nothing else: the 168 MiB of digits
+    are given back although their free is pending when shutdown is called."""
+    require_gpu()
+    say("[scratch] key switches only")
+    r = subprocess.run([sys.executable, "-c", ONLY_KEY_SWITCHES], cwd=ROOT, capture_output=True,
+                       text=True, timeout=100)
+    assert r.returncode == 0, r.stderr[-2000:]
+    held = int(r.stdout.split("HELD")[1])
+    assert held < 32 << 20, f"{held >> 20} MiB held after shutdown"
