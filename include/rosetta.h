@@ -162,8 +162,8 @@ rosetta_status rosetta_ksk_prepare(const uint64_t *ksk_std_dev, uint64_t *ksk_de
  * every other one that rotates (all but rosetta_pbs_batch_noalloc) works with
  * double-precision transforms, exactly: it expands the prepared key (to 3 or
  * 4 times its size) into stream-ordered memory of its own, from a pool that
- * keeps at most 256 MiB per device once the program has waited for the calls,
- * and that rosetta_shutdown() gives back.  Where that memory is not to be had, and while the
+ * keeps at most 4 GiB per device between calls and is given back by
+ * rosetta_shutdown().  Where that memory is not to be had, and while the
  * stream is being captured, the modular transforms run instead, with the
  * same output bits.  rosetta_trace expands its key, and the key switch of a
  * large batch keeps the digits of its ciphertexts (at most 512 MiB at a time),

@@ -1,7 +1,7 @@
 // Scratch memory of single calls: stream-ordered, from one pool per device,
 // so that calls on several streams or threads each have their own.  A pool
-// keeps what was freed, up to KEEP bytes, once a stream or the device is
-// waited for; scratch_release gives that back.
+// keeps what was freed, up to KEEP bytes, between calls; scratch_release
+// gives that back.
 #include <hip/hip_runtime.h>
 
 #include <map>
@@ -13,12 +13,7 @@ namespace rosetta {
 
 namespace {
 
-// Small, since nobody but rosetta_shutdown can take it back for the program's
-// own allocations: room for a key switch's digits (168 MiB for 14336
-// ciphertexts at the headline parameters; taking them anew after each wait
-// costs 0.26 of 1.6 ms) but not for an expanded bootstrapping key (576 MiB
-// there; taken anew 0.1 of 15.9 ms for a single ciphertext).
-constexpr uint64_t KEEP = (uint64_t)256 << 20;
+constexpr uint64_t KEEP = (uint64_t)4 << 30;
 std::mutex g_mu;
 std::map<int, hipMemPool_t> g_pools;
 
