@@ -46,6 +46,7 @@ rosetta_status ok() {
 }
 
 rosetta_status hip_fail(hipError_t e, const char *what) {
+  (void)hipGetLastError();  // (else the next call's launch check would return it)
   if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation)
     return fail(ROSETTA_ERR_NOMEM, "%s: %s", what, hipGetErrorString(e));
   return fail(ROSETTA_ERR_DEVICE, "%s: %s", what, hipGetErrorString(e));

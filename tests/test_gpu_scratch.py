@@ -1,10 +1,14 @@
 """The memory that calls take for themselves (stream-ordered, from one pool per
-device): what is given back, and when."""
+device): what is given back, and when; and what a call leaves behind that found
+no memory."""
 import os
 import subprocess
 import sys
 
+import numpy as np
 import pytest
+
+from paper_2609_16915_amd import rosetta as R
 
 from gpu_helpers import require_gpu, say
 
@@ -46,3 +50,25 @@ def test_shutdown_gives_back_what_key_switches_took():
     assert r.returncode == 0, r.stderr[-2000:]
     held = int(r.stdout.split("HELD")[1])
     assert held < 32 << 20, f"{held >> 20} MiB held after shutdown"
+
+
+def test_failed_call_leaves_no_error_for_the_next(O):
+    """A workspace larger than the device is refused, and the next call, with
+    one that fits, works (the inputs are as large as the batch says; nothing
+    is launched for it)."""
+    torch = require_gpu()
+    say("[scratch] workspace larger than the device")
+    prm = dict(n=1, k=1, N=4096, pbs_level=1, pbs_base_log=8, ks_level=1, ks_base_log=4, msg_bits=4)
+    rng = np.random.default_rng(4)
+    words = lambda *shape: rng.integers(0, R.P, shape, dtype=np.uint64)
+    bsk_std, ksk_std, lut, cts = words(R.bsk_words(prm)), words(R.ksk_words(prm)), words(4096), words(3, 2)
+    bsk = R.bsk_prepare(R.to_device(bsk_std), prm)
+    ksk = R.ksk_prepare(R.to_device(ksk_std), prm)
+    total = torch.cuda.get_device_properties(0).total_memory
+    batch = total // (4097 * 8) + 1
+    with pytest.raises(R.RosettaError) as e:
+        R.pbs_batch(torch.zeros((batch, 2), dtype=torch.int64, device="cuda"), bsk, ksk, R.to_device(lut), prm)
+    assert R.STATUS[e.value.status] == "ROSETTA_ERR_NOMEM"
+    got = R.to_host(R.pbs_batch(R.to_device(cts), bsk, ksk, R.to_device(lut), prm))
+    op = O.Params.make(**{k: v for k, v in prm.items() if k != "k"})
+    assert np.array_equal(got, O.pbs(op, cts, bsk_std, ksk_std, lut, O.NTT))
