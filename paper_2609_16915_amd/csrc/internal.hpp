@@ -167,6 +167,42 @@ inline bool ks_on_matrix_cores(const rosetta_params &p) {
   const uint64_t bound = (uint64_t)p.N * p.ks_level * (1ull << (p.ks_base_log - 1)) * 128;
   return bound < (1ull << 31);
 }
+// Which kernel switches a batch on a device of `cus` compute units.  (Times in
+// us with 256 CUs, calls back to back.)
+enum class KsRoute { VALU, SPLIT, DIGITS, MFMA };
+constexpr size_t KS_MFMA_ROWS = 128;  // ciphertexts of a workgroup of k_keyswitch_mfma
+inline KsRoute ks_route(const rosetta_params &p, size_t batch, size_t cus) {
+  if (!ks_on_matrix_cores(p)) return KsRoute::VALU;
+  const size_t cols = (p.n + 1 + 31) / 32, K = (size_t)p.N * p.ks_level;
+  // Few enough ciphertexts that every 16 of them and 32 columns have a CU
+  // (a workgroup of the split kernel fills one): there the split wins, 64
+  // ciphertexts 82 against 175 at the headline parameters; just past it,
+  // 128, it ties (178 against 175), at 1024 it loses (510 against 184).
+  if ((batch + 15) / 16 * cols <= cus) return KsRoute::SPLIT;
+  // Digits made once pay by being shared among column blocks and cost a pass
+  // over the batch and 28 us of host work (two launches, scratch).  Against
+  // them k_keyswitch_mfma takes one round of workgroups (about as long at any
+  // batch up to rows = cus), then two per CU.  Digits against that kernel:
+  const size_t rows = (batch + KS_MFMA_ROWS - 1) / KS_MFMA_ROWS;
+  // one or two column blocks and the chip filled: n = 50, N = 2048, 6 levels,
+  // 20480 / 28672 / 131072 ciphertexts 444 / 541 / 2722 against 494 / 493 /
+  // 2179; n = 20, N = 1024, 2 levels, 12288 / 16384 / 20480 ones 88 / 113 /
+  // 130 against 109 / 110 / 110; n = 20, N = 512, 1 level, 9000 / 12288 ones
+  // 37 / 50 against 39 / 40
+  if (cols <= 2 && 16 * rows > (K <= 1024 ? 5 : K <= 2048 ? 7 : 10) * cus) return KsRoute::MFMA;
+  // three, and two full workgroups per CU: n = 80, N = 512, 2 levels, 16384 /
+  // 20480 / 22528 ciphertexts 66 / 80 / 95 against 72 / 70 / 118
+  if (cols == 3 && K <= 1024 && 16 * rows * cols > 26 * cus && rows * cols <= 2 * cus)
+    return KsRoute::MFMA;
+  // the shortest contractions.  1 level, N = 256: up to 96 columns (n = 64, 1361 /
+  // 32768 / 65536 ciphertexts 29 / 63 / 110 against 18 / 50 / 95), or while the
+  // work is less than the host's (n = 1024, 896 / 1408 / 1920 ciphertexts, 231 /
+  // 363 / 495 workgroups, 30 / 29 / 30 against 21 / 29 / 32); 2 levels: n = 1024,
+  // 226 / 896 ciphertexts, 66 / 231 workgroups, 29 / 29 against 25 / 32
+  if (K == 256 && (cols <= 3 || 2 * rows * cols <= 3 * cus)) return KsRoute::MFMA;
+  if (p.N == 256 && p.ks_level == 2 && 2 * rows * cols <= cus) return KsRoute::MFMA;
+  return KsRoute::DIGITS;
+}
 // Words of the byte-plane key: ceil((n+1)/32) column blocks x N l_ks / 32
 // k blocks x 1024 words (16 operand fragments of 64 lanes x 8 bytes).
 inline size_t ks_matrix_key_words(const rosetta_params &p) {

@@ -159,8 +159,9 @@ __global__ void k_ksk_planes(const u64 *__restrict__ ksk, u64 *__restrict__ plan
 typedef int32_t ks_v4i __attribute__((ext_vector_type(4)));
 
 // out[b][c] = (c == n ? b'_b : 0) - sum_kappa D[b][kappa] K[kappa][c].
-// (The kernel for batches too large to be split while no scratch is to be
-// had: captured streams, the allocation-free entry point.)
+// (The kernel for batches too large to be split where digits made once do not
+// pay (ks_route) or no scratch is to be had: captured streams, the
+// allocation-free entry point.)
 // Workgroup = 4 waves on one 32-column block, each wave on its own 32
 // ciphertexts: two 16-ciphertext row tiles x two 16-column tiles x 8 byte
 // planes of int32 accumulators.  The contraction runs over k blocks in the
@@ -181,6 +182,7 @@ typedef int32_t ks_v4i __attribute__((ext_vector_type(4)));
 // the key fragments and the prefetched coefficients without spills (left
 // to itself the compiler takes 256 + 128 registers and one wave).
 constexpr int KSM_WAVES = 4;
+static_assert(32 * KSM_WAVES == KS_MFMA_ROWS, "ks_route counts these workgroups");
 
 template <int LKS>
 __global__ void __launch_bounds__(64 * KSM_WAVES) __attribute__((amdgpu_waves_per_eu(2, 2)))
@@ -655,18 +657,14 @@ static hipError_t launch_ks_gemm(const uint64_t *big, const uint64_t *ksk_dev, u
 hipError_t launch_keyswitch(const uint64_t *big, const uint64_t *ksk_dev, uint64_t *out,
                             size_t batch, const rosetta_params &p, bool may_allocate,
                             hipStream_t st) {
-  if (ks_on_matrix_cores(p)) {
-    // Few enough ciphertexts that every 16 of them and 32 columns have a CU
-    // (a workgroup of the split kernel fills one): there the split wins, 64
-    // ciphertexts 82 against 175 us at the headline parameters; just past it,
-    // 128, it ties (178 against 175), at 1024 it loses (510 against 184).
-    const size_t split = (batch + 15) / 16 * ((p.n + 1 + 31) / 32);
-    if (split <= (size_t)device_cus()) return launch_ks_small(big, ksk_dev, out, batch, p, st);
-    if (may_allocate) {
-      bool done = false;
-      const hipError_t e = launch_ks_gemm(big, ksk_dev, out, batch, p, st, done);
-      if (done) return e;
-    }
+  const KsRoute route = ks_route(p, batch, (size_t)device_cus());
+  if (route == KsRoute::SPLIT) return launch_ks_small(big, ksk_dev, out, batch, p, st);
+  if (route == KsRoute::DIGITS && may_allocate) {
+    bool done = false;
+    const hipError_t e = launch_ks_gemm(big, ksk_dev, out, batch, p, st, done);
+    if (done) return e;
+  }
+  if (route != KsRoute::VALU) {
     const dim3 grid((unsigned)((batch + 32 * KSM_WAVES - 1) / (32 * KSM_WAVES)),
                     (p.n + 1 + 31) / 32);
     const int n = (int)p.n, N = (int)p.N, beta = (int)p.ks_base_log;
