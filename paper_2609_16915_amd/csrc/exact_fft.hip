@@ -743,7 +743,8 @@ hipError_t launch_blind_rotate(const uint64_t *lwe_in, const uint64_t *bsk_dev,
 hipError_t launch_trace(const uint64_t *in, const uint64_t *autk_dev, uint64_t *out,
                         size_t batch, uint32_t N, int level, int base_log, const Tables &tb,
                         hipStream_t st) {
-  const int pieces = fft_pieces_for(N, level, base_log);
+  const int pieces =
+      trace_pieces(N, (unsigned)level, (unsigned)base_log, batch, (size_t)device_cus());
   if (pieces) {
     const size_t rounds = N == 2048 ? 11 : 12;
     if (void *key = scratch_take(rounds * 2 * pieces * level * (N / 2) * sizeof(cd), st)) {

@@ -109,6 +109,19 @@ inline int fft_pieces(const rosetta_params &p) {
   return pieces == 3 && p.pbs_level * p.pbs_base_log > 30 ? 4 : pieces;
 }
 
+// Pieces of the double-precision trace of a batch on a device of `cus` compute
+// units, 0 for the modular one.  A single level in four pieces takes eight
+// sums back for the one digit polynomial it transforms and pays only where
+// that hides: N = 2048, 13 bits, up to two workgroups per CU (256 / 513 / 14336
+// traces 123 / 250 / 3916 against 132 / 229 / 3620 us modular); N = 4096, 12
+// bits, past one per CU (256 / 513 / 14336 traces 233 / 624 / 11301 against
+// 215 / 631 / 11989).
+inline int trace_pieces(unsigned N, unsigned level, unsigned base_log, size_t batch, size_t cus) {
+  const int pieces = fft_pieces_for(N, level, base_log);
+  if (level == 1 && pieces == 4 && (N == 2048 ? batch > 2 * cus : batch <= cus)) return 0;
+  return pieces;
+}
+
 hipError_t launch_rows_prepare(const uint64_t *rows_std, uint64_t *rows_dev, size_t rows,
                                uint32_t N, const Tables &tb, hipStream_t st);
 // Trace: as launch_blind_rotate, with double-precision transforms where it can.

@@ -20,7 +20,10 @@ int main() {
   while (scanf("%15s %u %u %u %u %llu %llu", what, &n, &N, &l, &beta, &batch, &cus) == 7) {
     rosetta_params p{};
     p.n = n; p.k = 1; p.N = N; p.ks_level = p.pbs_level = l; p.ks_base_log = p.pbs_base_log = beta;
-    printf("%d\n", (int)ks_route(p, batch, cus));
+    if (!strcmp(what, "ks"))
+      printf("%d\n", (int)ks_route(p, batch, cus));
+    else
+      printf("%d\n", trace_pieces(N, l, beta, batch, cus));
   }
 }
 """
@@ -75,3 +78,35 @@ def test_key_switch_split_and_valu(rule):
     rows = [("ks", 1024, 2048, 6, 3, 112, CUS), ("ks", 1024, 2048, 6, 3, 113, CUS), ("ks", 31, 256, 3, 4, 4096, CUS),
             ("ks", 31, 256, 3, 4, 4097, CUS), ("ks", 64, 1024, 2, 9, 5, CUS)]
     assert rule(rows) == [SPLIT, DIGITS, SPLIT, DIGITS, VALU]
+
+
+# (N, level, base, batch): modular trace, double precision
+TRACE_MEASURED = [
+    ((2048, 1, 13, 1), 130, 118), ((2048, 1, 13, 256), 132, 123), ((2048, 1, 13, 512), 174, 178),
+    ((2048, 1, 13, 513), 229, 250), ((2048, 1, 13, 4096), 1077, 1157), ((2048, 1, 18, 1), 134, 117),
+    ((2048, 1, 18, 512), 183, 179), ((2048, 1, 18, 8192), 2188, 2276), ((4096, 1, 12, 1), 206, 219),
+    ((4096, 1, 12, 256), 215, 233), ((4096, 1, 12, 300), 424, 429), ((4096, 1, 12, 14336), 11989, 11301),
+    ((4096, 1, 17, 64), 220, 227), ((4096, 1, 17, 513), 656, 628), ((4096, 1, 17, 14336), 12324, 11320),
+    ((2048, 2, 17, 4096), 1557, 1304), ((4096, 2, 16, 1), 294, 239), ((2048, 4, 12, 14336), 7470, 5850),
+]
+
+
+def test_trace_takes_the_faster_kernel(rule):
+    got = rule([("tr", 1, *c, CUS) for c, _, _ in TRACE_MEASURED])
+    for (c, modular, double), pieces in zip(TRACE_MEASURED, got):
+        chosen, other = (double, modular) if pieces else (modular, double)
+        assert chosen <= 1.03 * other, (c, pieces)
+    assert set(got) == {0, 4}
+
+
+def test_trace_pieces_elsewhere_follow_the_bound(rule):
+    """Other levels, digit widths and rings keep what exactness allows, at any
+    batch."""
+    def bound(N, l, b):
+        holds = lambda bits: b + bits - 2 < 40 and l * N * 160 << (b + bits - 2) <= 1 << 51
+        return 0 if N < 2048 else 3 if holds(22) else 4 if holds(16) else 0
+    rows = [(N, l, b, batch) for N in (256, 1024, 2048, 4096) for l in (1, 2, 3, 4) for b in range(1, 31)
+            for batch in (1, 256, 257, 512, 513, 14336) if l * b <= 62]
+    for (N, l, b, batch), got in zip(rows, rule([("tr", 1, *r, CUS) for r in rows])):
+        want = bound(N, l, b)
+        assert got == want or (got, l, want) == (0, 1, 4), (N, l, b, batch)
