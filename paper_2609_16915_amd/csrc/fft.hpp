@@ -163,8 +163,8 @@ struct FftLane {
   }
 };
 // LDS by byte address.  The kernels that use these have dynamic LDS only, so
-// it starts at address 0.  (Through pointers the base is added once per
-// address, at run time.)
+// it starts at address 0 (test_code_objects_cpu.py holds the built library to
+// that).  (Through pointers the base is added once per address, at run time.)
 typedef double fft_v2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ cd fft_get(int at, int off) {
 #if defined(__HIP_DEVICE_COMPILE__)
