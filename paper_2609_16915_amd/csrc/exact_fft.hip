@@ -641,6 +641,7 @@ hipError_t launch_fft(const uint64_t *lwe_in, const uint64_t *bsk_dev, const uin
                       uint64_t *out, size_t batch, const rosetta_params &p, const Tables &tb,
                       int mode, int tp_glwe, cd *key, hipStream_t st) {
   const size_t xlds = F::TABLE_BYTES + (size_t)(S::TW_WORDS + S::XCHG_WORDS) * 8;
+  static_assert(br_fft_lds_bytes<F, L>(MAX_LWE_N) <= LDS_PER_CU, "room at every n");
   const size_t lds = br_fft_lds_bytes<F, L>((int)p.n);
   hipError_t e;
   if ((e = allow_lds(k_expand_key<S, F, P>, xlds)) != hipSuccess) return e;

@@ -14,6 +14,7 @@ namespace rosetta {
 // Largest LWE dimension the blind-rotation kernel accepts (its rounded
 // rotation amounts are staged in LDS).
 constexpr uint32_t MAX_LWE_N = 2048;
+constexpr size_t LDS_PER_CU = 160 * 1024;
 
 // Shape of the transform the kernels use at N = 2^logn: E = 2^ntt_le(logn)
 // elements per thread, pass 0 spanning ntt_first(logn) stages and every
@@ -89,7 +90,7 @@ void scratch_release();
 // the inverse is off by at most (4 (M - 2) + 2 + 7) u of the mean over
 // points of sum |D||K| (every path's roundings, the final twist included),
 // which is at most sum ||d|| ||k|| (Cauchy-Schwarz and Parseval).  Together
-// 146 u at N = 2048 and 158 u at N = 4096 for R = 6: 160 u.  With |d| <=
+// 146.4 u at N = 2048 and 159.2 u at N = 4096 for R = 6: 160 u.  With |d| <=
 // 2^(beta-1) and |k| <= 2^(b-1), ||d|| ||k|| <= N 2^(beta + b - 2), hence
 //   error <= R N 2^(beta + b - 2) 160 2^-53, wanted <= 1/4.
 // No input can exceed it: the bound holds for every digit and key word.

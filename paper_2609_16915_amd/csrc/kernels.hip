@@ -579,8 +579,6 @@ k_blind_rotate(const u64 *__restrict__ lwe_in, const u64 *__restrict__ bsk,
 //
 // Dynamic LDS: twiddles [TW_WORDS], accumulator [2N], the teams' exchange
 // buffers [2L][2N] (the products, [2][N], in the same words), rotation amounts.
-constexpr size_t LDS_PER_CU = 160 * 1024;
-
 template <class S, int L>
 constexpr size_t br_teams_lds_bytes(int n) {
   return (size_t)(S::TW_WORDS + 2 * S::N + 2 * L * S::XCHG_WORDS) * sizeof(u64) +
@@ -1064,11 +1062,11 @@ static hipError_t launch_br_levels(const uint64_t *lwe_in, const uint64_t *bsk_d
   // 326/331/512 us against 503/682/1294; N = 512, l = 3 1.11 ms against 1.57;
   // N = 1024, l = 1/2/4 0.37/1.48/2.55 ms (n = 33/64/64) against
   // 0.64/1.85/3.04.  With 768 the larger rings are slower in teams (1.67 ms
-  // against 1.54 at N = 512, l = 3).  A very large n leaves no room for the
-  // rotation amounts beside the products at N = 1024, l = 4.
+  // against 1.54 at N = 512, l = 3).
   if constexpr (S::LOGN <= 10) {
-    const size_t tlds = br_teams_lds_bytes<S, L>(n);
-    if (batch <= 2 * (size_t)device_cus() && tlds <= LDS_PER_CU) {
+    static_assert(br_teams_lds_bytes<S, L>(MAX_LWE_N) <= LDS_PER_CU, "room at every n");
+    if (batch <= 2 * (size_t)device_cus()) {
+      const size_t tlds = br_teams_lds_bytes<S, L>(n);
       if (L * beta <= 30)
         ROSETTA_LAUNCH((k_blind_rotate_teams<S, L, int32_t>), dim3(batch), dim3(2 * L * S::T), tlds,
                        st, lwe_in, bsk_dev, lut, out, n, beta, mode, tp_glwe, tb.zeta);
