@@ -29,9 +29,8 @@ int main() {
 """
 
 
-@pytest.fixture(scope="module")
-def rule(tmp_path_factory):
-    d = tmp_path_factory.mktemp("dispatch")
+def build_rule(d):
+    """Compile the rules in directory d; returns ask(rows), which runs them."""
     (d / "main.cpp").write_text(MAIN)
     subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
                     f"-I{ROOT}/include", f"-I{ROOT}/paper_2609_16915_amd/csrc", "main.cpp", "-o", "main"],
@@ -42,6 +41,11 @@ def rule(tmp_path_factory):
         out = subprocess.run([str(d / "main")], input=text, capture_output=True, text=True, check=True)
         return [int(x) for x in out.stdout.split()]
     return ask
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    return build_rule(tmp_path_factory.mktemp("dispatch"))
 
 
 VALU, SPLIT, DIGITS, MFMA = range(4)
