@@ -244,10 +244,11 @@ MIN_EXTRACTED_RATE = {"gpt2_gelu": 0.9999, "tinyllama_silu": 0.999, "llama3_8b_s
 
 
 def resident_workgroups(N: int) -> int:
-    """Blind-rotation workgroups the chip holds at once (256 CUs x 3
-    workgroups up to N = 2048, 2 at N = 4096): a batch runs in rounds of
-    this many ciphertexts."""
-    return 256 * (3 if N <= 2048 else 2)
+    """Blind-rotation workgroups of the workloads' kernel (double-precision
+    transforms, two waves per SIMD) the chip holds at once, 256 CUs x 2 at
+    N = 2048, x 1 at N = 4096: a batch runs in rounds of this many
+    ciphertexts."""
+    return 256 * {2048: 2, 4096: 1}[N]
 
 
 def dense_picks(batch: int, N: int, seed: int):
@@ -362,10 +363,15 @@ CORNERS = {
     # the headline ring with the largest small digits and a 64-bit rounded value
     "l3_b14_N2048": dict(n=12, N=2048, pbs_level=3, pbs_base_log=14, ks_level=3, ks_base_log=6,
                          msg_bits=2),
-    # the largest LWE dimension on the largest ring (the most LDS a blind
-    # rotation takes: 132 KiB), with the headline key switch
+    # the largest LWE dimension on the largest ring (the most LDS the blind
+    # rotations at N >= 2048 take: 148 KiB with double-precision transforms,
+    # 132 KiB with modular ones), with the headline key switch
     "n2048_N4096": dict(n=2048, N=4096, pbs_level=3, pbs_base_log=8, ks_level=6,
                         ks_base_log=3, msg_bits=2),
+    # the most LDS a blind rotation takes (156 KiB): few ciphertexts, the
+    # largest small ring, the most levels, the largest LWE dimension
+    "l4_b8_N1024_n2048": dict(n=2048, N=1024, pbs_level=4, pbs_base_log=8, ks_level=2, ks_base_log=4,
+                              msg_bits=2),
 }
 
 
@@ -387,18 +393,26 @@ def test_parameter_corners_bit_exact(O, torch_dev, name):
     ref_out, ref_big = O.pbs(op, cts, ks.bsk, ks.ksk, v, O.NTT, 0, want_big=True)
     assert np.array_equal(big, ref_big)
     assert np.array_equal(out, ref_out)
+    # the kernels that need no memory of their own (modular transforms also
+    # where the call above runs double-precision ones)
+    na = R.empty(out.shape)
+    R.pbs_batch_noalloc(R.to_device(cts), bsk, ksk, R.to_device(v), prm | {"k": 1}, na)
+    assert np.array_equal(R.to_host(na), ref_out)
 
 
 @pytest.mark.parametrize("level,beta", [(3, 8), (3, 15), (1, 20), (2, 16), (4, 7)])
 def test_n4096_two_instances_agree(O, torch_dev, level, beta):
-    """N = 4096 runs a batch that the CUs hold one workgroup each on the
-    blind-rotation instance compiled for two waves per SIMD, a larger one on
-    the four-wave instance (both with the accumulator in the transform
-    domain, at different register budgets): the first CU-count ciphertexts
-    of a batch one larger equal the same ciphertexts run alone, bit for bit
-    (both kernels, extracted and key-switched), and both ends equal the
-    oracle, for every level count (32- and 64-bit rounded values, digits
-    through the small and the general forward transform)."""
+    """N = 4096's modular transforms run a batch that the CUs hold one workgroup
+    each on the blind-rotation instance compiled for two waves per SIMD, a
+    larger one on the four-wave instance (both with the accumulator in the
+    transform domain, at different register budgets): the first CU-count
+    ciphertexts of a batch one larger equal the same ciphertexts run alone,
+    bit for bit, and both ends equal the oracle, for every level count (32-
+    and 64-bit rounded values, digits through the small and the general
+    forward transform).  The allocation-free call runs the modular transforms
+    for every one of these; the eager calls (extracted and key-switched) do
+    for 1 x 20, 2 x 16 and 4 x 7 bits and run the double-precision kernel for
+    3 x 8 and 3 x 15, which has one instance for both batches."""
     torch = torch_dev
     prm = dict(n=32, N=4096, pbs_level=level, pbs_base_log=beta, ks_level=3, ks_base_log=6,
                msg_bits=3, k=1)
@@ -418,6 +432,10 @@ def test_n4096_two_instances_agree(O, torch_dev, level, beta):
     out_cu = R.to_host(R.pbs_batch(R.to_device(cts[:cus]), bsk, ksk, d_v, prm))
     assert np.array_equal(big_all[:cus], big_cu)
     assert np.array_equal(out_all[:cus], out_cu)
+    for batch in (cus + 1, cus):
+        na = R.empty((batch, prm["n"] + 1))
+        R.pbs_batch_noalloc(R.to_device(cts[:batch]), bsk, ksk, d_v, prm, na)
+        assert np.array_equal(R.to_host(na), out_all[:batch])
     pick = [0, cus - 1, cus]
     ref_out, ref_big = O.pbs(op, cts[pick], ks.bsk, ks.ksk, v, O.NTT, 0, want_big=True)
     assert np.array_equal(big_all[pick], ref_big)
