@@ -85,18 +85,50 @@ def measured_traffic(workload: str, batch: int):
     return float(m_tb.group(1))
 
 
-def key_pieces(N: int, level: int, base_log: int) -> int:
-    """Pieces the key is cut into for double-precision transforms (the rule
-    of fft_pieces in csrc/internal.hpp), 0 where the modular ones run."""
-    if N not in (2048, 4096) or level > 3:
+def _pieces(N: int, rows: int, base_log: int) -> int:
+    """fft_pieces_for in csrc/internal.hpp."""
+    if N not in (2048, 4096):
         return 0
 
     def holds(bits):
-        return 2 * level * N * 160 << (base_log + bits - 2) <= 1 << 51
+        e = base_log + bits - 2
+        return e < 40 and rows * N * 160 << e <= 1 << 51
 
-    if level * base_log <= 30 and holds(22):
-        return 3
-    return 4 if holds(16) else 0
+    return 3 if holds(22) else 4 if holds(16) else 0
+
+
+def key_pieces(N: int, level: int, base_log: int) -> int:
+    """Pieces the key is cut into for the blind rotation's double-precision
+    transforms (the rule of fft_pieces in csrc/internal.hpp), 0 where the
+    modular ones run."""
+    if level > 3:
+        return 0
+    pieces = _pieces(N, 2 * level, base_log)
+    return 4 if pieces == 3 and level * base_log > 30 else pieces
+
+
+def trace_pieces(N: int, level: int, base_log: int, batch: int) -> int:
+    """The same for the trace (trace_pieces in csrc/internal.hpp)."""
+    pieces = _pieces(N, level, base_log)
+    if level == 1 and pieces == 4 and (batch > 2 * CU if N == 2048 else batch <= CU):
+        return 0
+    return pieces
+
+
+def keyswitch_kernel(n: int, N: int, level: int, base_log: int, batch: int) -> str:
+    """The kernel that switches a batch (ks_route in csrc/internal.hpp)."""
+    if not (1 <= base_log <= 7 and level * base_log <= 30 and N % 32 == 0
+            and N * level * (1 << (base_log - 1)) * 128 < (1 << 31)):
+        return "k_keyswitch"
+    cols, K, rows = (n + 32) // 32, N * level, -(-batch // 128)
+    if -(-batch // 16) * cols <= CU:
+        return "k_keyswitch_small"
+    if ((cols <= 2 and 16 * rows > (5 if K <= 1024 else 7 if K <= 2048 else 10) * CU)
+            or (cols == 3 and K <= 1024 and 16 * rows * cols > 26 * CU and rows * cols <= 2 * CU)
+            or (K == 256 and (cols <= 3 or 2 * rows * cols <= 3 * CU))
+            or (N == 256 and level == 2 and 2 * rows * cols <= CU)):
+        return "k_keyswitch_mfma"
+    return "k_keyswitch_gemm"
 
 
 def fft_flops(N: int, log_bfly: int, forward: int, inverse: int, products: int) -> int:
@@ -222,18 +254,24 @@ def lookup_select(R, W, w, p, keys, d_in, bsk, stream, steps):
     wall = (time.perf_counter() - t0) / steps
     br_ms = float(np.mean([a.elapsed_time(b) for a, b, _ in ev]))
     tr_ms = float(np.mean([b.elapsed_time(c) for _, b, c in ev]))
-    # (the trace's key is in 4 pieces at these parameters: log2 N rounds of
-    # TRACE_LEVEL forward and 2 x 4 inverse transforms)
-    rounds = int(math.log2(w.N))
-    tr_flops = w.batch * rounds * fft_flops(w.N, rounds - 1, TRACE_LEVEL, 8, 8 * TRACE_LEVEL)
-    tr_t = tr_flops / (tr_ms * 1e-3) / 1e12
+    rounds, pieces = int(math.log2(w.N)), trace_pieces(w.N, TRACE_LEVEL, TRACE_BASE_LOG, w.batch)
+    if pieces:
+        # log2 N rounds of TRACE_LEVEL forward and 2 inverse transforms per piece
+        tr_ops = w.batch * rounds * fft_flops(w.N, rounds - 1, TRACE_LEVEL, 2 * pieces,
+                                              2 * pieces * TRACE_LEVEL)
+        roofline = {"bound": "alu", "kernel": "k_trace_fft", "dtype": "f64", "key_pieces": pieces}
+        peak, unit, count = FP64_PEAK_T, "TFLOP/s", "per_launch_flops"
+    else:
+        tr_ops = w.batch * w.trace_modmul(TRACE_LEVEL)
+        roofline = {"bound": "alu", "kernel": "k_trace"}
+        peak, unit, count = MODMUL_PEAK_T, "Tmodmul/s", "per_launch_modmul"
+    tr_t = tr_ops / (tr_ms * 1e-3) / 1e12
+    roofline.update({"achieved": round(tr_t, 4), "peak": round(peak, 4), "unit": unit,
+                     "frac": round(tr_t / peak, 4), count: tr_ops, "launch_ms": round(tr_ms, 3)})
     return {"batch": w.batch, "trace_level": TRACE_LEVEL, "trace_base_log": TRACE_BASE_LOG,
             "selects_per_s": round(w.batch / wall, 2), "ms_per_step": round(wall * 1e3, 3),
             "kernels_ms": {"blind_rotate_glwe": round(br_ms, 3), "trace": round(tr_ms, 3)},
-            "roofline_trace": {"bound": "alu", "kernel": "k_trace_fft", "dtype": "f64",
-                               "achieved": round(tr_t, 4), "peak": round(FP64_PEAK_T, 4),
-                               "unit": "TFLOP/s", "frac": round(tr_t / FP64_PEAK_T, 4),
-                               "per_launch_flops": tr_flops, "launch_ms": round(tr_ms, 3)}}
+            "roofline_trace": roofline}
 
 
 def lookup_protocol(R, W, stream, steps, batch):
@@ -593,15 +631,14 @@ def main():
                      "multiplier_bound": round(MULTIPLIER_BOUND_T, 4),
                      "modmul_probe": round(probe_t, 4)})
     hbm_bytes = (w.bsk_words() + w.ksk_words()) * 8 + w.batch * 2 * (w.n + 1) * 8 + w.N * 8
-    # the key switch on the int8 matrix cores (the condition rosetta.h states
-    # for its byte-plane key): 8 byte-plane products of 2 ops per digit MAC
-    ks_mfma = (1 <= w.ks_base_log <= 7 and w.ks_level * w.ks_base_log <= 30 and w.N % 32 == 0
-               and w.N * w.ks_level * (1 << (w.ks_base_log - 1)) * 128 < (1 << 31))
+    ks_kernel = keyswitch_kernel(w.n, w.N, w.ks_level, w.ks_base_log, w.batch)
+    # (on the int8 matrix cores: 8 byte-plane products of 2 ops per digit MAC)
+    ks_mfma = ks_kernel != "k_keyswitch"
     # algorithmic work: one multiply and one add per digit MAC; the kernel
     # executes 8 byte-plane products per MAC (dense_equivalent_ops)
     ks_ops = 2 * w.batch * w.N * w.ks_level * (w.n + 1)
     ks_dense = 8 * ks_ops
-    roofline_ks = ({"bound": "mfma", "kernel": "k_keyswitch_gemm", "dtype": "i8",
+    roofline_ks = ({"bound": "mfma", "kernel": ks_kernel, "dtype": "i8",
                     "achieved": round(ks_ops / (ks_ms * 1e-3) / 1e15, 5),
                     "peak": INT8_PEAK_P, "unit": "POP/s",
                     "frac": round(ks_ops / (ks_ms * 1e-3) / 1e15 / INT8_PEAK_P, 5),

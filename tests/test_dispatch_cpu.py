@@ -22,6 +22,8 @@ int main() {
     p.n = n; p.k = 1; p.N = N; p.ks_level = p.pbs_level = l; p.ks_base_log = p.pbs_base_log = beta;
     if (!strcmp(what, "ks"))
       printf("%d\n", (int)ks_route(p, batch, cus));
+    else if (!strcmp(what, "br"))
+      printf("%d\n", fft_pieces(p));
     else
       printf("%d\n", trace_pieces(N, l, beta, batch, cus));
   }
@@ -114,3 +116,19 @@ def test_trace_pieces_elsewhere_follow_the_bound(rule):
     for (N, l, b, batch), got in zip(rows, rule([("tr", 1, *r, CUS) for r in rows])):
         want = bound(N, l, b)
         assert got == want or (got, l, want) == (0, 1, 4), (N, l, b, batch)
+
+
+def test_benchmark_names_the_kernels_of_these_rules(rule):
+    """bench.py states the rules again, for its rooflines."""
+    import bench
+    assert bench.CU == CUS
+    names = ["k_keyswitch", "k_keyswitch_small", "k_keyswitch_gemm", "k_keyswitch_mfma"]
+    ks = [(n, N, l, b, batch) for n in (1, 31, 32, 63, 64, 95, 96, 742, 1024, 2048) for N in (256, 512, 1024, 2048, 4096)
+          for l, b in ((1, 4), (1, 7), (2, 5), (3, 4), (6, 3), (3, 9))
+          for batch in (1, 16, 100, 257, 900, 2000, 5000, 10300, 14400, 18000, 21000, 70000)]
+    for c, got in zip(ks, rule([("ks", *c, CUS) for c in ks])):
+        assert bench.keyswitch_kernel(*c) == names[got], c
+    br = [(N, l, b, batch) for N in (256, 1024, 2048, 4096) for l in (1, 2, 3, 4) for b in range(1, 31)
+          for batch in (1, 256, 257, 512, 513) if l * b <= 62]
+    for c, pieces, tr in zip(br, rule([("br", 1, *c, CUS) for c in br]), rule([("tr", 1, *c, CUS) for c in br])):
+        assert bench.key_pieces(*c[:3]) == pieces and bench.trace_pieces(*c) == tr, c
