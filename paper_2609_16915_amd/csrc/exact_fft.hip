@@ -225,10 +225,10 @@ constexpr size_t br_fft_lds_bytes(int n) {
 // 1's digits during component 0's transforms, sum 0's first rows during
 // component 1's, the groups of sum S + 1 during sum S's inverse.
 //
-// Bound: VALU issue.  N = 2048, l = 3: 3.3k VALU instructions per wave and
+// Bound: VALU issue.  N = 2048, l = 3: 3.2k VALU instructions per wave and
 // step (9.3k with modular transforms), 1536 ciphertexts 62.0 ms against 96
 // ms; two workgroups share a CU (77 KB of LDS, 256 registers) and the
-// VALU issues 62 % of the time (21.2k clocks of a CU per step, against 34k
+// VALU issues 60 % of the time (21.4k clocks of a CU per step, against 34k
 // for a workgroup alone); without the key loads (a build that
 // computes something else) the step is 20 % shorter, with all keys in the L2
 // 3 %.  The lane swaps between the (7,6) and (5,4) passes beat a third

@@ -278,7 +278,7 @@ def test_full_workload_dense_parity(O, torch_dev, name):
     """The whole batch in the benchmark's launch configuration (blind
     rotation + extraction into one buffer, then the key switch, the two
     kernels rosetta_pbs_batch runs), compared with the oracle on at least 64
-    ciphertexts spread over every residency round the batch runs in (first,
+    ciphertexts spread over the residency rounds the batch runs in (first,
     second, last and partial last included), both the extracted and the
     key-switched ciphertexts of that one launch; then the single entry point
     on the same inputs: bit-identical to the pair (determinism across
