@@ -72,3 +72,34 @@ def test_failed_call_leaves_no_error_for_the_next(O):
     got = R.to_host(R.pbs_batch(R.to_device(cts), bsk, ksk, R.to_device(lut), prm))
     op = O.Params.make(**{k: v for k, v in prm.items() if k != "k"})
     assert np.array_equal(got, O.pbs(op, cts, bsk_std, ksk_std, lut, O.NTT))
+
+
+def test_no_room_for_the_expanded_key_runs_the_modular_kernel():
+    """With less memory free than the expanded key takes (3.2 GB at the largest
+    set), the call gives the words that the allocation-free one does, and the
+    same again once there is room."""
+    torch = require_gpu()
+    prm = dict(n=2048, k=1, N=4096, pbs_level=3, pbs_base_log=14, ks_level=1, ks_base_log=4, msg_bits=4)
+    rng = np.random.default_rng(5)
+    words = lambda *shape: R.to_device(rng.integers(0, R.P, shape, dtype=np.uint64))
+    bsk, ksk = R.bsk_prepare(words(R.bsk_words(prm)), prm), R.ksk_prepare(words(R.ksk_words(prm)), prm)
+    lut, cts, want = words(4096), words(3, 2049), R.empty((3, 2049))
+    out = R.empty((3, 2049))
+    R.pbs_batch_noalloc(cts, bsk, ksk, lut, prm, want)
+    ws = R.empty(R.pbs_workspace_bytes(prm, 3) // 8)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    R.shutdown()
+    held = torch.empty(torch.cuda.mem_get_info()[0] - (1500 << 20), dtype=torch.uint8, device="cuda")
+    say(f"[scratch] {torch.cuda.mem_get_info()[0] >> 20} MiB free")
+    try:
+        assert torch.cuda.mem_get_info()[0] < 3 << 30
+        R.pbs_batch_ws(cts, bsk, ksk, lut, prm, ws, out=out)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+    finally:
+        del held
+        torch.cuda.empty_cache()
+    R.pbs_batch_ws(cts, bsk, ksk, lut, prm, ws, out=out)
+    torch.cuda.synchronize()
+    assert torch.equal(out, want)
